@@ -1,0 +1,495 @@
+"""Workloads whose speed matters to a user of this package, for a timing harness.
+
+A stage case is one training step of one pipeline stage as bench.py and a training loop run it:
+delayed_update(t) issued first in the stage's overlap mode (it consumes the gradient of an earlier
+step), then the forward and backward of every microbatch of step t (1F1B order), then
+stage_join_update, after which the state views may be read.  The stage is in the middle of a run
+(stage_resume): moments, Error-Feedback buffers and the pending gradients are there.  A flat case is
+the update of a caller-held flat parameter vector: the gradient's norm and clip coefficient, then the
+fused update.
+
+listed() names the cases, draw(rng) gives more of the same ranges; prepare / run / work / tolerance /
+exact take a case.  exact() is plain torch in float64 (autograd for the stage) and shares no code
+with the package.
+"""
+from __future__ import annotations
+
+import math
+
+import torch
+
+DEV = "cuda:0"
+RMS_EPS, ROPE_THETA = 1e-5, 10000.0
+NEXT_T = 10  # the iteration the state is resumed at: bias correction well under way, EF active
+
+# ------------------------------------------------------------------------------------------ cases
+STAGE = dict(kind="stage", bf16=True, vocab=0, first=False, last=False, tied=False, micros=1, slots=1,
+             overlap=1, optimizer="adamw", delay=1)
+
+
+def _stage(name=None, **kw):
+    c = dict(STAGE, **kw)
+    if name:
+        c["name"] = name
+    return c
+
+
+def _flat(name=None, **kw):
+    c = dict(dict(kind="flat", g_bf16=True, shadow="bf16", optimizer="adamw", delay=1), **kw)
+    if name:
+        c["name"] = name
+    return c
+
+
+def listed():
+    small = dict(blocks=3, d=768, heads=12, kv=12, hd=64, ffn=3072, seq=1024, mb=8)
+    return [
+        # a whole tied fp32 model of debugging size: one step is some sixty launches
+        _stage("tiny-f32", bf16=False, blocks=2, d=128, heads=4, kv=4, hd=32, ffn=512, vocab=512, first=True,
+               last=True, tied=True, seq=64, mb=2),
+        # fp32 training of a small middle stage, where bf16 is not wanted
+        _stage("medium-f32", bf16=False, blocks=2, d=512, heads=8, kv=8, hd=64, ffn=2048, seq=256, mb=4),
+        # first stage of a small model (bench workload "small"): embedding, 8192 tokens
+        _stage("small-first", vocab=32000, first=True, **small),
+        # the same stage under delayed Muon: Newton-Schulz chains beside the step
+        _stage("small-muon", vocab=32000, first=True, optimizer="muon", **small),
+        # last stage of that model: untied head and cross-entropy at vocabulary 49152 (bench workload "last")
+        _stage("small-last", vocab=49152, last=True, **small),
+        # a last stage whose token count and vocabulary are no multiples of any tile
+        _stage("odd-last", vocab=32001, last=True, blocks=1, d=768, heads=12, kv=12, hd=64, ffn=3072, seq=333, mb=3),
+        # a grouped-query middle stage on sequences of an odd length
+        _stage("odd-middle", blocks=2, d=1024, heads=16, kv=4, hd=64, ffn=2816, seq=777, mb=3),
+        # middle stage of a 1B-class model (bench workload "mid")
+        _stage("mid-middle", blocks=4, d=2048, heads=16, kv=16, hd=128, ffn=8192, seq=2048, mb=4, overlap=2),
+        # one long sequence, grouped-query: attention weighs as much as the products
+        _stage("long-middle", blocks=2, d=2048, heads=16, kv=4, hd=128, ffn=5632, seq=8192, mb=1, overlap=2),
+        # middle stage of an 8B-class model (bench workload "large"), two microbatches in 1F1B order
+        _stage("large-1f1b", blocks=4, d=4096, heads=32, kv=8, hd=128, ffn=14336, seq=4096, mb=2, micros=2,
+               slots=2, overlap=2),
+        # the update of a 1e9-parameter shard from a bf16 gradient (bench's update-only workload)
+        _flat("update-1e9", n=1_000_000_000),
+        # a small odd-length shard with fp32 gradients and compute copy, NAdam
+        _flat("update-1e6", n=1_000_003, g_bf16=False, shadow="f32", optimizer="nadam"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.random()
+    if kind < 0.2:  # flat vectors from a few thousand elements up
+        opt = rng.choice(["adamw", "adamw", "nadam", "lion", "adan"])
+        return _flat(n=_log_int(rng, 4000, 600_000_000), g_bf16=rng.random() < 0.5,
+                     shadow=rng.choice(["bf16", "bf16", "f32", "none"]), optimizer=opt, delay=rng.choice([1, 1, 2]))
+    while True:
+        bf = kind < 0.85
+        d = rng.choice([256, 512, 640, 768, 1024, 1280, 1536, 2048, 2560, 4096] if bf else [128, 192, 256, 384, 512])
+        hd = rng.choice([64, 64, 128] if bf else [32, 64])
+        heads = max(1, d // hd)
+        kv = heads // rng.choice([g for g in (1, 1, 2, 4) if heads % g == 0])
+        ffn = 64 * max(2, round(d * rng.choice([2.67, 2.75, 3.5, 4.0]) / 64))
+        seq = _log_int(rng, 64, 4096) if bf else _log_int(rng, 32, 512)
+        if rng.random() < 0.5:
+            seq = 64 * max(1, round(seq / 64))
+        mb = rng.choice([1, 2, 3, 4, 8])
+        role = rng.choice(["first", "middle", "middle", "last"])
+        vocab = 0 if role == "middle" else _log_int(rng, 500, 50000 if bf else 2000)
+        if vocab and rng.random() < 0.5:
+            vocab = 128 * max(4, round(vocab / 128))
+        opt = rng.choice(["adamw", "adamw", "adamw", "nadam", "muon"]) if bf and d <= 1024 else "adamw"
+        micros = rng.choice([1, 1, 1, 2])
+        c = _stage(bf16=bf, blocks=rng.choice([1, 2, 3]), d=d, heads=heads, kv=kv, hd=hd, ffn=ffn, vocab=vocab,
+                   first=role == "first", last=role == "last", seq=seq, mb=mb, micros=micros, slots=micros,
+                   overlap=rng.choice([0, 1, 2]), optimizer=opt, delay=rng.choice([1, 1, 1, 2]))
+        whole = seq * mb % 128 == 0 and vocab % 128 == 0 and d % 128 == 0 and ffn % 128 == 0
+        # rates a plain program would reach bound the cost: a drawn step stays below the largest listed one
+        cap = 1.0e13 if bf and whole else 3.0e11 if bf else 5.0e10
+        if _stage_flops(c) <= cap:
+            return c
+
+
+# ---------------------------------------------------------------------------------------- geometry
+def _params(c):
+    """(name, shape) of every parameter in the order of the flat vector (every size a multiple of 64,
+    so the flat vector has no padding)."""
+    d, f, q, k = c["d"], c["ffn"], c["heads"] * c["hd"], c["kv"] * c["hd"]
+    out = [("embed", (c["vocab"], d))] if c["first"] else []
+    for i in range(c["blocks"]):
+        p = f"blk{i}."
+        out += [(p + "attn_norm", (d,)), (p + "wq", (q, d)), (p + "wk", (k, d)), (p + "wv", (k, d)),
+                (p + "wo", (d, q)), (p + "ffn_norm", (d,)), (p + "wgate", (f, d)), (p + "wup", (f, d)),
+                (p + "wdown", (d, f))]
+    if c["last"]:
+        out.append(("final_norm", (d,)))
+        if not c["tied"]:
+            out.append(("head", (c["vocab"], d)))
+    return out
+
+
+def _n_params(c):
+    return sum(math.prod(s) for _, s in _params(c))
+
+
+def _stage_flops(c):
+    """Forward and backward of the step's microbatches: three products per weight matrix and token, the
+    causal attention products (backward twice the forward), Muon's Newton-Schulz."""
+    T = c["seq"] * c["mb"] * c["micros"]
+    blk = c["d"] * c["hd"] * (2 * c["heads"] + 2 * c["kv"]) + 3 * c["d"] * c["ffn"]
+    attn = 3 * 4 * c["mb"] * c["micros"] * c["heads"] * c["hd"] * c["seq"] * (c["seq"] + 1) / 2
+    fl = c["blocks"] * (6.0 * T * blk + attn) + (6.0 * T * c["d"] * c["vocab"] if c["last"] else 0.0)
+    if c["optimizer"] == "muon":
+        for name, s in _params(c):
+            if name.startswith("blk") and len(s) == 2:
+                m, n = min(s), max(s)
+                fl += 5 * 2.0 * (2.0 * m * m * n + float(m) ** 3)
+    return fl
+
+
+def work(c):
+    if c["kind"] == "flat":
+        sh = {"bf16": 2, "f32": 4, "none": 0}[c["shadow"]]
+        state = 8 * (2 if c["optimizer"] == "lion" else 3) + 8 + (16 if c["optimizer"] == "adan" else 0)
+        return {"bytes": c["n"] * (state + (2 if c["g_bf16"] else 4) + sh), "flops": 20.0 * c["n"]}
+    n, T, es = _n_params(c), c["seq"] * c["mb"] * c["micros"], 2 if c["bf16"] else 4
+    # x, m, v and the EF buffer read and written, the pending gradient read, this step's written; the
+    # compute copy read and its successor written
+    b = n * (24 + 8 + 8 + 2 * es)
+    b += T * (8 if c["first"] else 2 * c["d"] * es)                              # tokens, or x_in and dx
+    b += T * (4 * c["vocab"] + 4 if c["last"] else 2 * c["d"] * es)              # logits, or y and dy
+    return {"bytes": b, "flops": _stage_flops(c)}
+
+
+def tolerance(c):
+    if c["kind"] == "flat":
+        # fp32 elementwise arithmetic; a bf16 copy may round the other way where x differs in its last bit
+        return {"rel": 1e-5, "max": 1e-2}
+    # bf16 activations and activation gradients through the stage's blocks; fp32 sums
+    return {"rel": 2e-2, "max": 0.8} if c["bf16"] else {"rel": 2e-5, "max": 1e-3}
+
+
+# ------------------------------------------------------------------------------------------ inputs
+def _hyper(c):
+    h = {"adamw": {}, "nadam": dict(beta2=0.999), "lion": dict(beta1=0.9, beta2=0.99, weight_decay=0.5),
+         "adan": dict(beta1=0.98, beta2=0.92, beta3=0.99), "muon": {}}[c["optimizer"]]
+    return dict(dict(lr=1e-3, beta1=0.9, beta2=0.95, eps=1e-8, weight_decay=0.1, clip_norm=1.0,
+                     ef_lambda=float(c["delay"]), delay=c["delay"]), **h)
+
+
+def _fill_state(c, n, gen, buf):
+    """Optimizer state in the middle of a run: gradients of norm 2 (so clipping at 1 halves them), moments
+    and Error-Feedback buffers of the sizes such gradients leave.  buf(name) is a flat vector of n
+    elements to fill."""
+    s = 1.0 / math.sqrt(n)
+    buf("m").normal_(0.0, 0.3 * s, generator=gen)
+    buf("v").uniform_(0.5 * s * s, 1.5 * s * s, generator=gen)
+    for j in range(c["delay"]):
+        buf(f"u{j}").normal_(0.0, 3e-4, generator=gen)
+        buf(f"g{j}").normal_(0.0, 2.0 * s, generator=gen)
+    if c["optimizer"] == "adan":
+        buf("adan_d").normal_(0.0, 0.1 * s, generator=gen)
+        buf("adan_gl").normal_(0.0, s, generator=gen)
+
+
+def _fill_weights(c, gen, x):
+    """Master weights: matrices N(0, 0.02), gains near 1."""
+    x.normal_(0.0, 0.02, generator=gen)
+    o = 0
+    for _, s in _params(c):
+        k = math.prod(s)
+        if len(s) == 1:
+            x[o:o + k].mul_(5.0).add_(1.0)
+        o += k
+
+
+def _batches(c, gen):
+    """The step's microbatches: tokens and targets uniform over the vocabulary, activations N(0, 1),
+    upstream gradients N(0, 1e-3)."""
+    dt = torch.bfloat16 if c["bf16"] else torch.float32
+    mb, s, d = c["mb"], c["seq"], c["d"]
+    out = []
+    for _ in range(c["micros"]):
+        b = {}
+        if c["first"]:
+            b["tokens"] = torch.randint(0, c["vocab"], (mb, s), generator=gen, device=DEV, dtype=torch.int32)
+        else:
+            b["x_in"] = torch.randn(mb, s, d, generator=gen, device=DEV).to(dt)
+        if c["last"]:
+            b["targets"] = torch.randint(0, c["vocab"], (mb, s), generator=gen, device=DEV, dtype=torch.int32)
+        else:
+            b["dy"] = torch.randn(mb, s, d, generator=gen, device=DEV).mul_(1e-3).to(dt)
+        out.append(b)
+    return out
+
+
+def _gen(seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(int(seed))
+    return g
+
+
+# ----------------------------------------------------------------------------------------- prepare
+def prepare(c, seed):
+    from paper_2606_30634_amd import binding as B
+    from paper_2606_30634_amd.stage import Stage, hparams, make_shape
+    gen = _gen(seed)
+    hp = hparams(optimizer=c["optimizer"], **_hyper(c))
+    tau = c["delay"]
+    if c["kind"] == "flat":
+        n = c["n"]
+        bufs = {}
+
+        def buf(name):
+            bufs[name] = torch.empty(n, device=DEV)
+            return bufs[name]
+
+        x = buf("x").normal_(0.0, 0.02, generator=gen)
+        _fill_state(c, n, gen, buf)
+        g = bufs["g0"].to(torch.bfloat16) if c["g_bf16"] else bufs["g0"]
+        sh = {"bf16": torch.bfloat16, "f32": torch.float32, "none": None}[c["shadow"]]
+        wsb = B.grad_norm_flat_workspace_bytes()
+        return dict(case=c, hp=hp, t=NEXT_T, n=n, x=x, g=g, m=bufs["m"], v=bufs["v"],
+                    u=[bufs[f"u{j}"] for j in range(tau)], d=bufs.get("adan_d"), gl=bufs.get("adan_gl"),
+                    shadow=None if sh is None else torch.empty(n, device=DEV, dtype=sh),
+                    norm=torch.zeros(2, device=DEV), flag=torch.zeros(1, dtype=torch.int32, device=DEV),
+                    ws=torch.empty(wsb, dtype=torch.uint8, device=DEV))
+    st = Stage(make_shape(c["blocks"], c["d"], c["heads"], c["kv"], c["hd"], c["ffn"], c["vocab"], c["first"],
+                          c["last"], c["tied"], c["seq"], c["mb"], c["slots"], bf16=c["bf16"], rms_eps=RMS_EPS,
+                          rope_theta=ROPE_THETA, muon=c["optimizer"] == "muon", max_delay=tau,
+                          adan=c["optimizer"] == "adan"), DEV)
+    names = {"m": "flat.m", "v": "flat.v", "adan_d": "flat.adan_d", "adan_gl": "flat.adan_gprev"}
+    for j in range(tau):
+        names[f"u{j}"] = "flat.u_prev" if j == 0 else f"flat.u_prev{j}"
+        names[f"g{j}"] = f"flat.grad{(NEXT_T - tau + j) % (tau + 1)}"
+    _fill_weights(c, gen, st.view("flat.master"))
+    _fill_state(c, _n_params(c), gen, lambda name: st.view(names[name]))
+    st.resume(NEXT_T, tau)
+    st.set_update_overlap(c["overlap"])
+    per = _batches(c, gen)
+    for b in per:
+        if not c["last"]:
+            b["y"] = torch.empty_like(b["dy"])
+        if not c["first"]:
+            b["dx"] = torch.empty_like(b["x_in"])
+        b["loss"] = torch.zeros(1, device=DEV)
+    order, f, warm = [], 0, c["slots"] - 1
+    for i in range(c["micros"]):
+        while f < min(c["micros"], i + 1 + warm):
+            order.append(("F", f))
+            f += 1
+        order.append(("B", i))
+    return dict(case=c, stage=st, hp=hp, t=NEXT_T, per=per, order=order, ng=tau + 1,
+                x=st.view("flat.master"), m=st.view("flat.m"), v=st.view("flat.v"),
+                u=[st.view(names[f"u{j}"]) for j in range(tau)],
+                g=[st.view(f"flat.grad{j}") for j in range(tau + 1)],
+                logits=[st.view(f"act{i}.logits") for i in range(c["slots"])] if c["last"] else None)
+
+
+# --------------------------------------------------------------------------------------------- run
+def _run_flat(s):
+    from paper_2606_30634_amd import binding as B
+    c, t, n = s["case"], s["t"], s["n"]
+    s["t"] = t + 1
+    stream = torch.cuda.current_stream().cuda_stream
+    u = s["u"][t % c["delay"]]
+    sh = s["shadow"]
+    B.grad_norm_flat(n, s["g"].data_ptr(), c["g_bf16"], 1.0, s["norm"].data_ptr(), s["flag"].data_ptr(),
+                     s["ws"].data_ptr(), s["ws"].numel(), stream)
+    head = (n, s["x"].data_ptr(), s["g"].data_ptr(), c["g_bf16"], s["m"].data_ptr(), s["v"].data_ptr())
+    tail = (u.data_ptr(), None if sh is None else sh.data_ptr(), c["shadow"] == "bf16", t, s["hp"],
+            s["norm"].data_ptr() + 4, stream)
+    if c["optimizer"] == "adan":
+        B.delayed_update_flat_adan(*head, s["d"].data_ptr(), s["gl"].data_ptr(), *tail)
+    else:
+        B.delayed_update_flat(*head, *tail)
+    return {"x": s["x"], "m": s["m"], "v": s["v"], "u": u, "norm": s["norm"], "shadow": sh, "adan": [s["d"], s["gl"]]}
+
+
+def run(s):
+    c = s["case"]
+    if c["kind"] == "flat":
+        return _run_flat(s)
+    st, t = s["stage"], s["t"]
+    s["t"] = t + 1
+    st.update(t, s["hp"])
+    for kind, i in s["order"]:
+        b = s["per"][i]
+        if kind == "F":
+            st.forward(i % c["slots"], t, tokens=b.get("tokens"), x_in=b.get("x_in"), targets=b.get("targets"),
+                       y_out=b.get("y"), loss=b["loss"] if c["last"] else None)
+        else:
+            st.backward(i % c["slots"], dy=b.get("dy"), dx_out=b.get("dx"), microbatches_per_step=c["micros"])
+    st.join_update()
+    return {"grad": s["g"][t % s["ng"]], "x": s["x"], "m": s["m"], "v": s["v"], "u": s["u"],
+            "y": [b.get("y") for b in s["per"]], "dx": [b.get("dx") for b in s["per"]],
+            "loss": [b["loss"] for b in s["per"]] if c["last"] else None, "logits": s["logits"]}
+
+
+# ------------------------------------------------------------------------------------------- exact
+def _exact_update(c, x, st, k, t, muon_mats=()):
+    """The delayed rule in float64, in place on x and the state: iteration t, k-th applied update."""
+    h = _hyper(c)
+    tau, lam, lr, wd, eps = c["delay"], h["ef_lambda"], h["lr"], h["weight_decay"], h["eps"]
+    b1, b2 = (float(torch.tensor(h[q], dtype=torch.float32)) for q in ("beta1", "beta2"))  # the ABI's fp32 values
+    g = st["g0"]
+    norm = float(g.norm())
+    cl = min(1.0, h["clip_norm"] / (norm + 1e-6))
+    gg = g * cl
+    m, v = st["m"], st["v"]
+    if c["optimizer"] == "lion":
+        u = lr * (torch.sign(b1 * m + (1 - b1) * gg) + wd * x)
+        m.mul_(b2).add_(gg, alpha=1 - b2)
+    elif c["optimizer"] == "adan":
+        b3 = float(torch.tensor(h["beta3"], dtype=torch.float32))
+        diff = gg - st["adan_gl"]
+        m.mul_(b1).add_(gg, alpha=1 - b1)
+        st["adan_d"].mul_(b2).add_(diff, alpha=1 - b2)
+        v.mul_(b3).add_((gg + b2 * diff) ** 2, alpha=1 - b3)
+        u = lr * ((m / (1 - b1 ** k) + b2 * st["adan_d"] / (1 - b2 ** k)) / ((v / (1 - b3 ** k)).sqrt() + eps) + wd * x)
+        st["adan_gl"].copy_(gg)
+    else:
+        m0, v0 = (m.clone(), v.clone()) if muon_mats else (None, None)
+        m.mul_(b1).add_(gg, alpha=1 - b1)
+        v.mul_(b2).add_(gg * gg, alpha=1 - b2)
+        if c["optimizer"] == "nadam":
+            mu = lambda j: b1 * (1.0 - 0.5 * 0.96 ** (j * 0.004))  # noqa: E731
+            P = math.prod(mu(j) for j in range(1, k + 1))
+            up = (1 - mu(k)) / (1 - P) * gg + mu(k + 1) / (1 - P * mu(k + 1)) * m
+            u = lr * (up / ((v / (1 - b2 ** k)).sqrt() + eps) + wd * x)
+        else:
+            u = lr * ((m / (1 - b1 ** k)) / ((v / (1 - b2 ** k)).sqrt() + eps) + wd * x)
+        for o, (r, q) in muon_mats:  # delayed Muon on the blocks' matrices: their second moment stays as it was
+            sl = slice(o, o + r * q)
+            m[sl] = 0.95 * m0[sl] + 0.05 * gg[sl]
+            v[sl] = v0[sl]
+            X = m[sl].view(r, q)
+            X = X.t() if r > q else X
+            X = X / (X.norm() + 1e-7)
+            for _ in range(5):
+                A = X @ X.t()
+                X = 3.4445 * X + (-4.7750 * A + 2.0315 * (A @ A)) @ X
+            X = X.t() if r > q else X
+            u[sl] = lr * (0.2 * math.sqrt(max(r, q)) * X.reshape(-1) + wd * x[sl])
+    ub = st[f"u{t % tau}"]
+    x.sub_((1 + lam) * u - lam * ub)
+    ub.copy_(u)
+    return norm, cl
+
+
+def _rms(x, gain):
+    return x * torch.rsqrt((x * x).mean(-1, keepdim=True) + RMS_EPS) * gain
+
+
+def _rope(x):  # [s, heads, hd]
+    s, _, hd = x.shape
+    i = torch.arange(hd // 2, device=x.device, dtype=torch.float64)
+    ang = torch.arange(s, device=x.device, dtype=torch.float64)[:, None] * ROPE_THETA ** (-2.0 * i / hd)
+    co, si = ang.cos()[:, None], ang.sin()[:, None]
+    a, b = x[..., : hd // 2], x[..., hd // 2:]
+    return torch.cat([a * co - b * si, b * co + a * si], -1)
+
+
+def _block(c, w, x):
+    """One decoder block on one sequence [s, d] in float64."""
+    s, hd, Hq, Hk = x.shape[0], c["hd"], c["heads"], c["kv"]
+    n1 = _rms(x, w[0])
+    q = _rope((n1 @ w[1].t()).view(s, Hq, hd)).transpose(0, 1)
+    k = _rope((n1 @ w[2].t()).view(s, Hk, hd)).repeat_interleave(Hq // Hk, 1).transpose(0, 1)
+    v = (n1 @ w[3].t()).view(s, Hk, hd).repeat_interleave(Hq // Hk, 1).transpose(0, 1)
+    sc = (q @ k.transpose(1, 2)) / math.sqrt(hd)
+    sc = sc.masked_fill(torch.ones(s, s, dtype=torch.bool, device=x.device).triu(1), float("-inf"))
+    o = (sc.softmax(-1) @ v).transpose(0, 1).reshape(s, Hq * hd)
+    h = x + o @ w[4].t()
+    n2 = _rms(h, w[5])
+    return h + (torch.nn.functional.silu(n2 @ w[6].t()) * (n2 @ w[7].t())) @ w[8].t()
+
+
+def exact(c, seed):
+    if not torch.cuda.is_available():
+        return None
+    gen = _gen(seed)
+    tau, bufs = c["delay"], {}
+    n = c["n"] if c["kind"] == "flat" else _n_params(c)
+
+    def buf(name):
+        bufs[name] = torch.empty(n, device=DEV)
+        return bufs[name]
+
+    if c["kind"] == "flat":
+        x32 = buf("x").normal_(0.0, 0.02, generator=gen)
+        _fill_state(c, n, gen, buf)
+        if c["g_bf16"]:
+            bufs["g0"] = bufs["g0"].to(torch.bfloat16)
+        if n > 200_000_000:
+            return None  # the float64 copies and their temporaries would not fit beside each other
+        st = {k: v.double() for k, v in bufs.items() if k != "x"}
+        x = x32.double()
+        norm, cl = _exact_update(c, x, st, NEXT_T - tau + 1, NEXT_T)
+        return {"x": x, "m": st["m"], "v": st["v"], "u": st[f"u{NEXT_T % tau}"],
+                "norm": torch.tensor([norm, cl], dtype=torch.float64), "shadow": None if c["shadow"] == "none" else x,
+                "adan": [st.get("adan_d"), st.get("adan_gl")]}
+    x32 = buf("x")
+    _fill_weights(c, gen, x32)
+    _fill_state(c, n, gen, buf)
+    per = _batches(c, gen)
+    # the step's weights: the compute copy
+    names = _params(c)
+    wts, o, mats = {}, 0, []
+    for name, s in names:
+        k = math.prod(s)
+        w = x32[o:o + k].view(s)
+        wts[name] = (w.to(torch.bfloat16) if c["bf16"] else w).double()
+        if c["optimizer"] == "muon" and name.startswith("blk") and len(s) == 2:
+            mats.append((o, s))
+        o += k
+    grads = {name: torch.zeros(s, dtype=torch.float64, device=DEV) for name, s in names}
+    blk = ["attn_norm", "wq", "wk", "wv", "wo", "ffn_norm", "wgate", "wup", "wdown"]
+    out = {"y": [], "dx": [], "loss": [], "logits": []}
+    head = "embed" if c["tied"] else "head"
+    for b in per:
+        ys, dxs, losses, logs = [], [], 0.0, []
+        for q in range(c["mb"]):
+            xs = [wts["embed"][b["tokens"][q].long()] if c["first"] else b["x_in"][q].double()]
+            with torch.no_grad():
+                for i in range(c["blocks"]):
+                    xs.append(_block(c, [wts[f"blk{i}.{z}"] for z in blk], xs[-1]))
+            if c["last"]:
+                leaf = [t.detach().requires_grad_() for t in (xs[-1], wts["final_norm"], wts[head])]
+                z = _rms(leaf[0], leaf[1]) @ leaf[2].t()
+                ce = torch.nn.functional.cross_entropy(z, b["targets"][q].long(), reduction="sum") / (c["mb"] * c["seq"])
+                dy, gn, gh = torch.autograd.grad(ce / c["micros"], leaf)
+                grads["final_norm"] += gn
+                grads[head] += gh
+                losses += float(ce)
+                logs.append(z.detach().float())
+            else:
+                ys.append(xs[-1])
+                dy = b["dy"][q].double()
+            for i in reversed(range(c["blocks"])):
+                leaf = [t.detach().requires_grad_() for t in [xs[i]] + [wts[f"blk{i}.{z}"] for z in blk]]
+                with torch.enable_grad():
+                    got = torch.autograd.grad(_block(c, leaf[1:], leaf[0]), leaf, dy)
+                dy = got[0]
+                for z, g in zip(blk, got[1:]):
+                    grads[f"blk{i}.{z}"] += g
+            if c["first"]:
+                grads["embed"].index_add_(0, b["tokens"][q].long(), dy)
+            else:
+                dxs.append(dy)
+        out["y"].append(torch.stack(ys) if ys else None)
+        out["dx"].append(torch.stack(dxs) if dxs else None)
+        out["loss"].append(torch.tensor([losses], dtype=torch.float64))
+        out["logits"].append(torch.cat(logs).reshape(-1) if logs else None)
+    if not c["last"]:
+        out["loss"] = out["logits"] = None
+    out["grad"] = torch.cat([grads[name].reshape(-1) for name, _ in names])
+    del grads, wts
+    if n > 400_000_000:  # as for the flat vectors; the gradient and the activations are compared
+        out.update(x=None, m=None, v=None, u=None)
+        return out
+    st = {k: v.double() for k, v in bufs.items() if k != "x"}
+    x = x32.double()
+    _exact_update(c, x, st, NEXT_T - tau + 1, NEXT_T, mats)
+    out.update(x=x, m=st["m"], v=st["v"], u=[st[f"u{j}"] for j in range(tau)])
+    return out
