@@ -103,6 +103,20 @@ __device__ __forceinline__ void dma4(const void* base, uint32_t voff, uint32_t l
   asm volatile("global_load_lds_dword %0, %1" ::"v"(voff), "s"(base), "{m0}"(lds) : "memory");
 }
 
+// The same 16-byte load with a range: a raw buffer descriptor over [base, end) (base wave-uniform;
+// end - base clamped to 2 GB), and lanes whose 16 bytes start past the range write zeros.  BUFFER_OUT
+// is an offset that no range holds.
+constexpr uint32_t BUFFER_OUT = 0x80000000u;
+__device__ __forceinline__ u32x4 buffer_range(const void* base, const void* end) {
+  const uint64_t a = (uint64_t)(uintptr_t)base;
+  const int64_t n = (const char*)end - (const char*)base;
+  const uint32_t bytes = n <= 0 ? 0u : n > 0x7fffffffll ? 0x7ffffff0u : (uint32_t)n;
+  return u32x4{(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
+}
+__device__ __forceinline__ void dma16_range(u32x4 range, uint32_t voff, uint32_t lds) {
+  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(range), "{m0}"(lds) : "memory");
+}
+
 __device__ __forceinline__ void block_barrier() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();

@@ -564,8 +564,11 @@ __global__ void __launch_bounds__(256) embed_scatter(const T* __restrict__ dx0,
 // Cross-entropy of one row of logits z [V] (one block per row), in two passes over the fp32
 // logits: the forward keeps a running (max m, sum s of exp(z - m)) per thread over 16-byte
 // chunks, merges the pairs across the block in a fixed order and writes lse = m + log s and the
-// row's loss lse - z[target]; the backward writes (exp(z - lse) - onehot) scale.  A target outside
-// [0, V) is ignored: zero loss and zero gradient.
+// row's loss lse - z[target]; the backward writes (exp(z - lse) - onehot) scale into rows of ld >= V
+// elements (ld a multiple of 4, zeros past V).  Rows of any V are read as 16-byte vectors (a row of
+// an odd V starts on a 4-byte boundary, which vector loads take).  A target outside [0, V) is
+// ignored: zero loss and zero gradient.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {
   const float mm = fmaxf(m, m2);
   if (mm == -INFINITY) return;  // both empty
@@ -579,17 +582,14 @@ __global__ void __launch_bounds__(256) ce_fwd_rows(const float* __restrict__ log
   __shared__ float sm_m[4], sm_s[4];
   const float* z = logits + (int64_t)blockIdx.x * V;
   float m = -INFINITY, s = 0.f;
-  if ((V & 3) == 0) {
-    const f32x4* z4 = reinterpret_cast<const f32x4*>(z);
-    for (int j = threadIdx.x; j < V / 4; j += 256) {
-      const f32x4 v = z4[j];
-      const float mm = fmaxf(m, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
-      s = s * __expf(m - mm) + (__expf(v[0] - mm) + __expf(v[1] - mm)) + (__expf(v[2] - mm) + __expf(v[3] - mm));
-      m = mm;
-    }
-  } else {
-    for (int j = threadIdx.x; j < V; j += 256) lse_merge(m, s, z[j], 1.f);
+  const f32x4u* z4 = reinterpret_cast<const f32x4u*>(z);
+  for (int j = threadIdx.x; j < V / 4; j += 256) {
+    const f32x4 v = z4[j];
+    const float mm = fmaxf(m, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+    s = s * __expf(m - mm) + (__expf(v[0] - mm) + __expf(v[1] - mm)) + (__expf(v[2] - mm) + __expf(v[3] - mm));
+    m = mm;
   }
+  if ((int)threadIdx.x < V % 4) lse_merge(m, s, z[V - V % 4 + threadIdx.x], 1.f);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     const float m2 = __shfl_xor(m, o, WAVE), s2 = __shfl_xor(s, o, WAVE);
@@ -614,32 +614,30 @@ template <typename T>
 __global__ void __launch_bounds__(256) ce_bwd_rows(const float* __restrict__ logits,
                                                    const int32_t* __restrict__ tg,
                                                    const float* __restrict__ lse, int V, float scale,
-                                                   T* __restrict__ dlog) {
-  const int64_t base = (int64_t)blockIdx.x * V;
+                                                   T* __restrict__ dlog, int ld) {
+  const float* z = logits + (int64_t)blockIdx.x * V;
+  T* dz = dlog + (int64_t)blockIdx.x * ld;
   const int t = tg[blockIdx.x];
   const bool valid = t >= 0 && t < V;
   const float l = lse[blockIdx.x];
   const float sc = valid ? scale : 0.f;
-  if ((V & 3) == 0) {
-    const f32x4* z4 = reinterpret_cast<const f32x4*>(logits + base);
-    for (int j = threadIdx.x; j < V / 4; j += 256) {
-      const f32x4 v = z4[j];
-      float p[4];
+  const f32x4u* z4 = reinterpret_cast<const f32x4u*>(z);
+  for (int j = threadIdx.x; j < V / 4; j += 256) {
+    const f32x4 v = z4[j];
+    float p[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) p[q] = __expf(v[q] - l) * sc - (4 * j + q == t ? sc : 0.f);
-      if constexpr (sizeof(T) == 2) {
-        bf16x4 o;
+    for (int q = 0; q < 4; ++q) p[q] = __expf(v[q] - l) * sc - (4 * j + q == t ? sc : 0.f);
+    if constexpr (sizeof(T) == 2) {
+      bf16x4 o;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = (bf16)p[q];
-        *reinterpret_cast<bf16x4*>(dlog + base + 4 * j) = o;
-      } else {
-        *reinterpret_cast<f32x4*>(dlog + base + 4 * j) = f32x4{p[0], p[1], p[2], p[3]};
-      }
+      for (int q = 0; q < 4; ++q) o[q] = (bf16)p[q];
+      *reinterpret_cast<bf16x4*>(dz + 4 * j) = o;
+    } else {
+      *reinterpret_cast<f32x4*>(dz + 4 * j) = f32x4{p[0], p[1], p[2], p[3]};
     }
-  } else {
-    for (int j = threadIdx.x; j < V; j += 256)
-      dlog[base + j] = from_f32<T>(__expf(logits[base + j] - l) * sc - (j == t ? sc : 0.f));
   }
+  const int j = V - V % 4 + threadIdx.x;  // the last V mod 4 logits, then zeros up to ld
+  if (j < ld) dz[j] = j < V ? from_f32<T>(__expf(z[j] - l) * sc - (j == t ? sc : 0.f)) : from_f32<T>(0.f);
 }
 
 __global__ void __launch_bounds__(1024) mean_kernel(const float* __restrict__ v, int n,
@@ -829,12 +827,12 @@ void launch_ce_fwd(const float* logits, const int32_t* targets, int rows, int vo
 }
 template <typename T>
 static void ce_bwd_t(const float* logits, const int32_t* tg, const float* lse, int rows, int V, float scale,
-                     void* dl, hipStream_t st) {
-  if (rows > 0) ce_bwd_rows<T><<<rows, 256, 0, st>>>(logits, tg, lse, V, scale, (T*)dl);
+                     void* dl, int ld, hipStream_t st) {
+  if (rows > 0) ce_bwd_rows<T><<<rows, 256, 0, st>>>(logits, tg, lse, V, scale, (T*)dl, ld);
 }
 void launch_ce_bwd(bool bf, const float* logits, const int32_t* targets, const float* lse, int rows, int vocab,
-                   float scale, void* dlogits, hipStream_t st) {
-  DISPATCH(bf, ce_bwd_t, logits, targets, lse, rows, vocab, scale, dlogits, st);
+                   float scale, void* dlogits, int ld, hipStream_t st) {
+  DISPATCH(bf, ce_bwd_t, logits, targets, lse, rows, vocab, scale, dlogits, ld, st);
 }
 void launch_mean(const float* v, int n, float* out, hipStream_t st) {
   mean_kernel<<<1, 1024, 0, st>>>(v, n, out);

@@ -8,121 +8,19 @@
 //   - an operand whose global layout is row-contiguous (W in dy W, both operands of dy^T x) is
 //     staged as it sits in memory ([k][row], 16-byte chunks) and its fragments are read with
 //     gfx950's transposing LDS read ds_read_b64_tr_b16.
-// Block tile BM x BN x 64 over 4 waves of WM x WN, two LDS stages: the next k-slice is fetched into
-// registers while the current one feeds the MFMAs, then written to the other stage; one barrier per
-// k-slice.  Inside a k-slice the fragments of the next 16-deep step are read from LDS while the
-// MFMAs of the current one run.  Rows are padded by 16 bytes so the 16-byte fragment reads of 32
-// rows spread over the banks.  Full tiles use loaders without bounds checks.  The epilogue stages
-// each wave's tile through LDS, 32 rows at a time, and writes 16-byte rows (residual and beta
-// terms read the same way).  Block order is remapped so that consecutive tiles of one output row
-// band land on one XCD (one L2).  Deterministic split-K for underfilled fp32-output products.
+// Block tiles are 128 x 128 (4 waves of 64 x 64) or 256 x 256 (8 waves of 64 x 128) with 64-deep
+// k-slices that go straight from global memory to LDS.  Inside a k-slice the fragments of the next
+// 16-deep step are read from LDS while the MFMAs of the current one run.  The epilogue stages each
+// wave's tile through LDS and writes 16-byte rows.  Block order is remapped so that consecutive
+// tiles of one output row band land on one XCD (one L2).  Deterministic split-K for underfilled
+// fp32-output products.
 #include "common.h"
 #include "kernels.h"
 #include <algorithm>
 
 namespace {
 
-constexpr int BK = 64;
-constexpr int PADK = BK + 8;  // LDS row pitch in elements
-
-template <int ROWS, int NT, bool KMAJ, bool CHECK>
-struct TileLoader;
-
-// k-contiguous operand: chunks of 8 consecutive k of one row (16-byte loads and stores)
-template <int ROWS, int NT, bool CHECK>
-struct TileLoader<ROWS, NT, true, CHECK> {
-  static constexpr int CHUNKS = ROWS * BK / 8;
-  static constexpr int PER = CHUNKS / NT;
-  static_assert(CHUNKS % NT == 0, "tile does not split evenly over the threads");
-  u32x4 r[PER];
-
-  __device__ __forceinline__ void load(const bf16* __restrict__ G, int ld, int row0, int nrows, int k0,
-                                       int K) {
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int c = threadIdx.x + p * NT;
-      const int gr = row0 + c / (BK / 8), gk = k0 + (c % (BK / 8)) * 8;
-      const bool ok = !CHECK || (gr < nrows && gk < K);
-      const u32x4 v = ok ? *reinterpret_cast<const u32x4*>(G + (int64_t)gr * ld + gk) : u32x4{0u, 0u, 0u, 0u};
-      r[p] = v;
-    }
-  }
-  __device__ __forceinline__ void store_one(bf16* __restrict__ S, int p) const {
-    const int c = threadIdx.x + p * NT;
-    *reinterpret_cast<u32x4*>(S + (c / (BK / 8)) * PADK + (c % (BK / 8)) * 8) = r[p];
-  }
-  __device__ __forceinline__ void store(bf16* __restrict__ S) const {
-#pragma unroll
-    for (int p = 0; p < PER; ++p) store_one(S, p);
-  }
-};
-
-// row-contiguous operand: kept as it sits in memory, a [k][row] tile of pitch ROWS + 32 filled
-// with 16-byte chunks of 8 rows; its MFMA fragments are read with transposing LDS reads.  One
-// such read by half a wave covers 4 k-rows x 32 rows (16 dwords per k-row); a pitch of 16 dwords
-// mod 64 puts those four runs on disjoint banks.
-template <int ROWS>
-constexpr int row_pitch() { return ROWS + 32; }
-
-template <int ROWS, int NT, bool CHECK>
-struct TileLoader<ROWS, NT, false, CHECK> {
-  static constexpr int CHUNKS = ROWS * BK / 8;
-  static constexpr int PER = CHUNKS / NT;
-  static constexpr int PR = row_pitch<ROWS>();
-  static_assert(CHUNKS % NT == 0, "tile does not split evenly over the threads");
-  u32x4 r[PER];
-
-  __device__ __forceinline__ void load(const bf16* __restrict__ G, int ld, int row0, int nrows, int k0,
-                                       int K) {
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int c = threadIdx.x + p * NT;
-      const int gk = k0 + c / (ROWS / 8), gr = row0 + (c % (ROWS / 8)) * 8;
-      const bool ok = !CHECK || (gr < nrows && gk < K);  // nrows is a multiple of 8
-      r[p] = ok ? *reinterpret_cast<const u32x4*>(G + (int64_t)gk * ld + gr) : u32x4{0u, 0u, 0u, 0u};
-    }
-  }
-  __device__ __forceinline__ void store_one(bf16* __restrict__ S, int p) const {
-    const int c = threadIdx.x + p * NT;
-    *reinterpret_cast<u32x4*>(S + (c / (ROWS / 8)) * PR + (c % (ROWS / 8)) * 8) = r[p];
-  }
-  __device__ __forceinline__ void store(bf16* __restrict__ S) const {
-#pragma unroll
-    for (int p = 0; p < PER; ++p) store_one(S, p);
-  }
-};
-
-// LDS elements of one stage of an operand tile
-template <int ROWS, bool KMAJ>
-constexpr int stage_elems() { return KMAJ ? ROWS * PADK : BK * row_pitch<ROWS>(); }
-
-// MFMA fragment: row r0 + lane mod 32 of the tile, k = k0 + 8 (lane / 32) .. +7
-template <int ROWS, bool KMAJ>
-__device__ __forceinline__ bf16x8 frag(const bf16* T, int r0, int k0) {
-  if constexpr (KMAJ) {
-    const int l = threadIdx.x % 64;
-    return *reinterpret_cast<const bf16x8*>(T + (r0 + l % 32) * PADK + k0 + 8 * (l / 32));
-  } else {
-    return frag_tr(T, row_pitch<ROWS>(), r0, k0);
-  }
-}
-
-template <int BM, int BN, int WM, int WN, bool AK = true, bool BKM = true>
-struct Cfg {
-  static constexpr int NW = (BM / WM) * (BN / WN);
-  static constexpr int NT = NW * 64;
-  static constexpr int FM = WM / 32, FN = WN / 32;
-  static constexpr int SA = stage_elems<BM, AK>(), SB = stage_elems<BN, BKM>();
-  static constexpr size_t main_lds = (size_t)2 * (SA + SB) * sizeof(bf16);
-  static constexpr int EP = WN + 4;  // epilogue staging pitch (fp32 elements)
-  static constexpr size_t epi_lds = (size_t)NW * 16 * EP * sizeof(float);
-  static constexpr size_t lds = main_lds > epi_lds ? main_lds : epi_lds;
-};
-
-// Waves per SIMD the tile allows (accumulators and LDS stages): told to the compiler so that it
-// schedules for that occupancy instead of trading the fragment prefetch for registers.
-template <int BM, int BN>
-constexpr int tile_waves_per_simd() { return BM * BN >= 256 * 256 ? 1 : 2; }
+constexpr int BKT = 64;  // depth of a k-slice
 
 // XCD-aware tile order: hardware places block b on XCD b mod 8; give each XCD a contiguous run
 // of tiles, walked in groups of GM row tiles (down a group's rows, then to its next column), so
@@ -134,7 +32,7 @@ __device__ __forceinline__ void tile_origin(const GemmArgs& g, int b, int& m0, i
   const int tiles_n = (g.N + BN - 1) / BN;
   const int tiles_m = (g.M + BM - 1) / BM;
   const int nblk = tiles_m * tiles_n;
-  if ((nblk & 7) == 0) b = (b & 7) * (nblk >> 3) + (b >> 3);
+  b = (b & 7) * (nblk >> 3) + min(b & 7, nblk & 7) + (b >> 3);
   const int first_m = (b / (GM * tiles_n)) * GM;
   const int gsz = min(tiles_m - first_m, GM);
   m0 = (first_m + (b % (GM * tiles_n)) % gsz) * BM;
@@ -154,135 +52,6 @@ __device__ __forceinline__ void tri_origin(const GemmArgs& g, int b, int& m0, in
   }
   m0 = i * BM;
   n0 = (i + b - first) * BN;
-}
-
-// Epilogue: per RP-row part (RP = 16 or 8) of each 32-row fragment row of the wave tile, stage
-// the fp32 accumulators through the wave's own LDS area and write 16-byte rows: split-K partials
-// to the workspace, or C with the beta / residual / SwiGLU-backward / RoPE / delta /
-// SwiGLU-forward terms.  A wave reads back only what it wrote, and one wave's LDS operations
-// complete in issue order, so no barrier is needed between the parts and the global stores are
-// never waited for here.  The staging area (NW x RP x (WN + 4) floats) must be free: every wave
-// past its last read of it.
-template <int BM, int BN, int WM, int WN, typename OutT, bool CHECK, int RP = 16>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[WM / 32][WN / 32],
-                                              float* stage, int m0, int n0, int wm0, int wn0) {
-  static_assert(RP == 16 || RP == 8, "staging part of 8 or 16 rows");
-  constexpr int FM = WM / 32, FN = WN / 32;
-  constexpr int EP = WN + 4;  // staging pitch (fp32 elements)
-  constexpr int NP = 32 / RP, EPP = 16 / NP;  // parts per fragment row, accumulators per part
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  float* stg = stage + wave * RP * EP;
-  const bool split = g.ksplit > 1;
-  float* W = split ? g.ws + (int64_t)blockIdx.y * g.M * g.N : nullptr;
-  OutT* C = (OutT*)g.C;
-  const bf16* R = (const bf16*)g.resid;
-  constexpr int VEC = sizeof(OutT) == 2 ? 8 : 4;  // elements per 16-byte store
-  static_for<FM * NP>([&](auto IH) {
-    constexpr int i = IH / NP, h = IH % NP;
-    // accumulator e of lane l holds fragment row 8 (e / 4) + 4 (l / 32) + e mod 4: rows
-    // RP h .. RP h + RP - 1 are e = EPP h .. EPP h + EPP - 1
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int e = EPP * h; e < EPP * h + EPP; ++e)
-        stg[(8 * (e / 4) - RP * h + 4 * (lane / 32) + (e % 4)) * EP + j * 32 + lane % 32] = acc[i][j][e];
-    asm volatile("" ::: "memory");
-    const int rbase = m0 + wm0 + i * 32 + RP * h;
-    if (split) {
-      for (int c = lane; c < RP * WN / 4; c += 64) {
-        const int r = c / (WN / 4), cc = (c % (WN / 4)) * 4;
-        const int row = rbase + r, col = n0 + wn0 + cc;
-        if (!CHECK || (row < g.M && col < g.N))
-          *reinterpret_cast<float4*>(W + (int64_t)row * g.N + col) = *reinterpret_cast<const float4*>(stg + r * EP + cc);
-      }
-    } else {
-      for (int c = lane; c < RP * WN / VEC; c += 64) {
-        const int r = c / (WN / VEC), cc = (c % (WN / VEC)) * VEC;
-        const int row = rbase + r, col = n0 + wn0 + cc;
-        if (CHECK && (row >= g.M || col >= g.N)) continue;  // N is a multiple of 8
-        const int64_t o = (int64_t)row * g.ldc + col;
-        float v[VEC];
-#pragma unroll
-        for (int q = 0; q < VEC; ++q) v[q] = stg[r * EP + cc + q];
-        if constexpr (sizeof(OutT) == 4) {
-          if (g.beta != 0.f) {
-            const float4 old = *reinterpret_cast<const float4*>((const float*)C + o);
-            v[0] += g.beta * old.x; v[1] += g.beta * old.y; v[2] += g.beta * old.z; v[3] += g.beta * old.w;
-          }
-          *reinterpret_cast<float4*>((float*)C + o) = make_float4(v[0], v[1], v[2], v[3]);
-        } else if (g.epi == 1) {  // SwiGLU backward from dz = v
-          const bf16* gu = (const bf16*)g.aux + (int64_t)row * g.ld_aux + col;
-          const bf16x8 av = *reinterpret_cast<const bf16x8*>(gu);
-          const bf16x8 bv = *reinterpret_cast<const bf16x8*>(gu + g.N);
-          bf16x8 da, db;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const float a = (float)av[q], bb = (float)bv[q];
-            const float sg = 1.0f / (1.0f + __expf(-a));
-            da[q] = (bf16)(v[q] * bb * sg * (1.0f + a * (1.0f - sg)));
-            db[q] = (bf16)(v[q] * a * sg);
-          }
-          *reinterpret_cast<bf16x8*>((bf16*)C + o) = da;
-          *reinterpret_cast<bf16x8*>((bf16*)C + o + g.N) = db;
-        } else if (g.epi == 4) {  // dO, plus delta = rowsum(dO O) over each head's columns
-          bf16x8 ov;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) ov[q] = (bf16)v[q];
-          *reinterpret_cast<bf16x8*>((bf16*)C + o) = ov;
-          const bf16x8 ob = *reinterpret_cast<const bf16x8*>((const bf16*)g.aux + (int64_t)row * g.ld_aux + col);
-          float dot = 0.f;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) dot += (float)ov[q] * (float)ob[q];
-          // the head's delta_hd / 8 chunks sit in consecutive lanes (aligned groups)
-          for (int m = 1; m < g.delta_hd / 8; m <<= 1) dot += __shfl_xor(dot, m, 64);
-          if (col % g.delta_hd == 0) {
-            const int bb = row / g.delta_S, ii = row % g.delta_S, hh = col / g.delta_hd;
-            g.delta[((int64_t)bb * (g.N / g.delta_hd) + hh) * g.delta_S + ii] = dot;
-          }
-        } else if (g.epi == 3) {  // SwiGLU forward: panel column col is gate or up of z column zc
-          const int grp = col / 32, zc = (grp / 2) * 32 + col % 32;
-          bf16x8 ov;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) ov[q] = (bf16)v[q];
-          bf16* Cb = (bf16*)C + (int64_t)row * g.ldc;
-          if ((grp & 1) == 0) {
-            *reinterpret_cast<bf16x8*>(Cb + zc) = ov;
-            const float* up = stg + r * EP + cc + 32;  // the up values of the same z columns
-            bf16x8 zv;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) zv[q] = (bf16)(v[q] / (1.0f + __expf(-v[q])) * up[q]);
-            *reinterpret_cast<bf16x8*>((bf16*)g.out2 + (int64_t)row * g.ld_out2 + zc) = zv;
-          } else {
-            *reinterpret_cast<bf16x8*>(Cb + g.glu + zc) = ov;
-          }
-        } else if (g.epi == 2 && col < g.rope_cols) {  // RoPE on the fp32 products
-          const int hd = g.rope_hd, hh = hd / 2;
-          const int c = col % hd, i0 = c % hh;
-          const bool first = c < hh;
-          const float* xp = stg + r * EP + (first ? cc + hh : cc - hh);  // partner columns
-          const int64_t tb = (int64_t)(row % g.rope_S) * hh + i0;
-          bf16x8 ov;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const float cs = g.rope_cos[tb + q], sn = g.rope_sin[tb + q];
-            ov[q] = (bf16)(first ? v[q] * cs - xp[q] * sn : v[q] * cs + xp[q] * sn);
-          }
-          *reinterpret_cast<bf16x8*>((bf16*)C + o) = ov;
-        } else {
-          if (R) {
-            const bf16x8 rr = *reinterpret_cast<const bf16x8*>(R + o);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] += (float)rr[q];
-          }
-          bf16x8 ov;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) ov[q] = (bf16)v[q];
-          *reinterpret_cast<bf16x8*>((bf16*)C + o) = ov;
-        }
-      }
-    }
-    asm volatile("" ::: "memory");
-  });
 }
 
 // Epilogue kinds of the direct-to-LDS kernels (compile-time; the numbers of the first five are
@@ -352,18 +121,22 @@ __device__ __forceinline__ void epi_load(EpiIn<EPI>& in, const GemmArgs& g, int 
   }
 }
 
-__device__ __forceinline__ float sigmoid_fast(float a) {
-  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * a));
+// RAG: the correctly rounded divide (partial tiles are few, whole ones bound by their stores)
+template <bool RAG>
+__device__ __forceinline__ float sigmoid(float a) {
+  if constexpr (RAG) return 1.0f / (1.0f + __expf(-a));
+  else return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * a));
 }
 
-// Epilogue of the direct-to-LDS kernels (full tiles).  Per RP-row part of each 32-row fragment
+// Epilogue of the direct-to-LDS kernels (RAG: the tile may reach past C; only chunks inside it are
+// read and written, and fp32 rows that do not start on 16 bytes leave element by element).  Per RP-row part of each 32-row fragment
 // row of the wave tile: the accumulators go through the wave's own LDS staging area and leave as
 // 16-byte rows.  The global operands the epilogue kind reads are all requested before the first
 // part is written (or one part ahead, where the registers for all of them would not fit), so their
 // latency is paid about once per tile instead of once per part.  A wave reads back only what it wrote and
 // its LDS operations complete in issue order: no barrier between parts, and the stores are never
 // waited for here.  The staging area (waves x RP x (WN + 4) floats) must be free.
-template <int BM, int BN, int WM, int WN, typename OutT, int EPI, int RP>
+template <int BM, int BN, int WM, int WN, typename OutT, int EPI, int RP, bool RAG>
 __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM / 32][WN / 32],
                                              float* stage, int m0, int n0, int wm0, int wn0) {
   static_assert(RP == 16 || RP == 8, "staging part of 8 or 16 rows");
@@ -403,7 +176,8 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM
     for (int j = 0; j < CPL; ++j) {
       int r, cc, row, col;
       chunk(p, j, r, cc, row, col);
-      epi_load<EPI>(in[p % RS][j], g, row, col);
+      if (!RAG || (row < g.M && col < g.N)) epi_load<EPI>(in[p % RS][j], g, row, col);
+      else in[p % RS][j] = EpiIn<EPI>{};
     }
   };
   if constexpr (PD > 0) static_for<(PD < NPART ? PD : NPART)>(request);
@@ -423,11 +197,21 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM
       int r, cc, row, col;
       chunk(p, j, r, cc, row, col);
       const EpiIn<EPI>& x = in[p % RS][j];
+      if (RAG && (row >= g.M || col >= g.N)) continue;  // bf16 output: N is a multiple of 8
       float v[VEC];
 #pragma unroll
       for (int q = 0; q < VEC; ++q) v[q] = stg[r * EP + cc + q];
       if constexpr (sizeof(OutT) == 4) {
-        if (split) {
+        if (RAG && (g.N | (split ? 0 : g.ldc)) % 4 != 0) {
+          for (int q = 0; q < 4 && col + q < g.N; ++q) {
+            if (split) {
+              W[(int64_t)row * g.N + col + q] = v[q];
+            } else {
+              float* c = (float*)g.C + (int64_t)row * g.ldc + col + q;
+              *c = g.beta != 0.f ? v[q] + g.beta * *c : v[q];
+            }
+          }
+        } else if (split) {
           st_nt(W + (int64_t)row * g.N + col, make_float4(v[0], v[1], v[2], v[3]));
         } else {
           float* Cf = (float*)g.C + (int64_t)row * g.ldc + col;
@@ -445,7 +229,7 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM
 #pragma unroll
           for (int q = 0; q < 8; ++q) {
             const float a = (float)x.a[q], bb = (float)x.b[q];
-            const float sg = sigmoid_fast(a);
+            const float sg = sigmoid<RAG>(a);
             da[q] = (bf16)(v[q] * bb * sg * (1.0f + a * (1.0f - sg)));
             db[q] = (bf16)(v[q] * a * sg);
           }
@@ -476,7 +260,15 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM
             const float* up = stg + r * EP + cc + 32;  // the up values of the same z columns
             bf16x8 zv;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) zv[q] = (bf16)(v[q] * sigmoid_fast(v[q]) * up[q]);
+            for (int q = 0; q < 8; ++q) {
+              // RAG: z of the stored gate and up, as the SwiGLU kernel makes it
+              if constexpr (RAG) {
+                const float gt = (float)ov[q];
+                zv[q] = (bf16)(gt * (1.0f / (1.0f + expf(-gt))) * (float)(bf16)up[q]);
+              } else {
+                zv[q] = (bf16)(v[q] * sigmoid<RAG>(v[q]) * up[q]);
+              }
+            }
             st_nt((bf16*)g.out2 + (int64_t)row * g.ld_out2 + zc, zv);
           } else {
             st_nt(Crow + g.glu + zc, ov);
@@ -536,7 +328,7 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM
       }
     }
     if constexpr (EPI == EPI_PLAIN && sizeof(OutT) == 2) {
-      if (g.sym && m0 != n0) {
+      if (!RAG && g.sym && m0 != n0) {
         // symmetric product, a tile above the diagonal: the part again at C[col, row], as 8-row
         // column segments of the staged rows
         constexpr int CT = WN * (RP / 8) / 64;  // segments per lane
@@ -557,110 +349,8 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM
   });
 }
 
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename OutT, bool CHECK>
-__global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
-__attribute__((amdgpu_waves_per_eu(tile_waves_per_simd<BM, BN>(), tile_waves_per_simd<BM, BN>())))
-gemm_mfma_kernel(GemmArgs g) {
-  using C_ = Cfg<BM, BN, WM, WN, AK, BKM>;
-  constexpr int WAVES_N = BN / WN;
-  constexpr int NT = C_::NT, FM = C_::FM, FN = C_::FN, SA = C_::SA, SB = C_::SB;
-  extern __shared__ __align__(16) unsigned char smem[];
-  bf16* As = reinterpret_cast<bf16*>(smem);                 // [2][SA]
-  bf16* Bs = As + 2 * SA;                                   // [2][SB]
-
-  int m0, n0;
-  tile_origin<BM, BN>(g, blockIdx.x, m0, n0);
-
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
-
-  f32x16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  TileLoader<BM, NT, AK, CHECK> la;
-  TileLoader<BN, NT, BKM, CHECK> lb;
-  const bf16* A = (const bf16*)g.A;
-  const bf16* B = (const bf16*)g.B;
-  // split-K: this block covers k in [kbeg, kend); kbeg is a multiple of BK
-  int kbeg = 0, kend = g.K;
-  if (g.ksplit > 1) {
-    const int chunk = ((g.K + g.ksplit - 1) / g.ksplit + BK - 1) / BK * BK;
-    kbeg = blockIdx.y * chunk;
-    kend = min(g.K, kbeg + chunk);
-  }
-  const int nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
-  la.load(A, g.lda, m0, g.M, kbeg, kend);
-  lb.load(B, g.ldb, n0, g.N, kbeg, kend);
-  la.store(As);
-  lb.store(Bs);
-  __syncthreads();
-  // Per k-slice, in this order (the compiler may not move instructions across the fences):
-  //   step 0: global loads of the next slice, then the fragment reads of step 1, then the MFMAs
-  //   steps 1, 2: fragment reads of the following step, then the MFMAs
-  //   step 3: the MFMAs, each followed by its share of the LDS writes of the next slice
-  // so every fragment read has a whole step of MFMAs to land, and the global loads three.
-  constexpr int NM = FM * FN;
-  constexpr int PA = decltype(la)::PER, PB = decltype(lb)::PER;
-  constexpr int WPM = (PA + PB + NM - 1) / NM;  // LDS writes per MFMA in the last step
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    // next slice (the last iteration reloads its own slice, unused, so the loads and the LDS
-    // writes are unconditional)
-    const int kn = kbeg + min(kt + 1, nk - 1) * BK;
-    const bf16* as = As + cur * SA;
-    const bf16* bs = Bs + cur * SB;
-    bf16* asn = As + (cur ^ 1) * SA;
-    bf16* bsn = Bs + (cur ^ 1) * SB;
-    bf16x8 af[2][FM], bfr[2][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i) af[0][i] = frag<BM, AK>(as, wm0 + i * 32, 0);
-#pragma unroll
-    for (int j = 0; j < FN; ++j) bfr[0][j] = frag<BN, BKM>(bs, wn0 + j * 32, 0);
-    static_for<BK / 16>([&](auto KS) {
-      constexpr int ks = KS, c = ks & 1;
-      if constexpr (ks == 0) {
-        la.load(A, g.lda, m0, g.M, kn, kend);
-        lb.load(B, g.ldb, n0, g.N, kn, kend);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if constexpr (ks + 1 < BK / 16) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i) af[c ^ 1][i] = frag<BM, AK>(as, wm0 + i * 32, (ks + 1) * 16);
-#pragma unroll
-        for (int j = 0; j < FN; ++j) bfr[c ^ 1][j] = frag<BN, BKM>(bs, wn0 + j * 32, (ks + 1) * 16);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[c][i], bfr[c][j], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      } else {
-        static_for<NM>([&](auto Q) {
-          constexpr int q = Q, i = q / FN, j = q % FN;
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[c][i], bfr[c][j], acc[i][j], 0, 0, 0);
-          static_for<WPM>([&](auto W) {
-            constexpr int w = q * WPM + W;
-            if constexpr (w < PA) la.store_one(asn, w);
-            else if constexpr (w < PA + PB) lb.store_one(bsn, w - PA);
-          });
-          __builtin_amdgcn_sched_barrier(0);
-        });
-      }
-    });
-    __syncthreads();
-  }
-
-  gemm_epilogue<BM, BN, WM, WN, OutT, CHECK>(g, acc, reinterpret_cast<float*>(smem), m0, n0, wm0, wn0);
-}
-
 // ---------------------------------------------------------------------------------------------
-// Full-tile kernel with direct-to-LDS operand loads (gfx950 global_load_lds_dwordx4): each lane's
+// Kernel with direct-to-LDS operand loads (gfx950 global_load_lds_dwordx4): each lane's
 // 16 bytes land at the wave's LDS base + 16 * lane, so a tile is written in lane order and the
 // bank spreading is an XOR swizzle of 16-byte chunks instead of padding:
 //   k-contiguous tile [ROWS][BKT]: chunk kc of row r sits at r * BKT/8 + (kc ^ ((r / (128/BKT)) mod
@@ -668,6 +358,14 @@ gemm_mfma_kernel(GemmArgs g) {
 //   row-contiguous tile [BKT][ROWS]: chunk rc of k-row k sits at k * ROWS/8 + (rc ^ 4 (k mod 4)), so
 //     the 4 k-rows x 32 rows of one half-wave transposing read fall in 4 different 64-byte bank
 //     groups (ROWS >= 128, a whole number of 256-byte bank periods per k-row).
+// RAG: any M, N, K (the same pipeline; whole products keep the kernels without ranges and predicates,
+// whose epilogue stores need not be waited for).  It replaced a register-staged kernel (M, N, K
+// multiples of 8) and, for the rest, an fp32 FMA tiling: T = 2331 tokens, d 1024, d_ffn 2816, a
+// block's twelve products 5.2 ms -> 0.39 ms (405 TFLOP/s; latency of 152-tile grids); T = 999,
+// vocabulary 32001, the head's three 9.5 -> 0.54 ms.  The loads are buffer loads whose range ends with the operand, so rows past it
+// land in LDS as zeros, and so do the k chunks of a k-contiguous operand past K (their lanes get an
+// offset no range holds); columns past a row-contiguous operand's edge bring its next row, which
+// only reaches outputs outside C.
 // NS stages: the loads of slice kt + NS - 1 are issued while slice kt is consumed, so a load has
 // NS - 1 slices of MFMAs to land; one barrier per slice, after each thread has seen its own loads
 // of the slice complete (vmcnt), makes every thread's loads of it visible.
@@ -750,7 +448,7 @@ constexpr int dma_waves_per_simd() {
 // count, so that every tile of a block maps to the block's XCD).  The slices of all its tiles form
 // one sequence: the loads of slice G + NS - 1 of that sequence (the next tile's first slices near
 // the end of a tile) are issued while slice G is consumed, into stage (G + NS - 1) mod NS.
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename OutT, int BKT, int NS, int EPI>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename OutT, int BKT, int NS, int EPI, bool RAG>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
 __attribute__((amdgpu_waves_per_eu(dma_waves_per_simd<BM, BN, WM, WN, AK, BKM, BKT, NS>(),
                                    dma_waves_per_simd<BM, BN, WM, WN, AK, BKM, BKT, NS>())))
@@ -771,20 +469,23 @@ gemm_dma_kernel(GemmArgs g) {
   // vector-memory operations one thread's epilogue issues at least: one per 16-byte output chunk
   constexpr int RP = C_::RP, CPP = RP * WN / (sizeof(OutT) == 2 ? 8 : 4);  // 16-byte chunks per part
   static_assert(CPP % 64 == 0, "every lane stores the same number of chunks per part");
-  constexpr int EPI_OPS = FM * (32 / RP) * (CPP / 64);
+  // (RAG: a wave outside C issues none)
+  constexpr int EPI_OPS = RAG ? 0 : FM * (32 / RP) * (CPP / 64);
   static_assert((NS - 2) * (PA + PB) + EPI_OPS < 64, "vmcnt range");
   extern __shared__ __align__(16) unsigned char smem[];
   bf16* S = reinterpret_cast<bf16*>(smem);  // [NS][A tile | B tile]
 
-  const int tiles = g.sym ? (g.M / BM) * (g.M / BM + 1) / 2 : (g.M / BM) * (g.N / BN);
+  const int tiles = !RAG && g.sym ? (g.M / BM) * (g.M / BM + 1) / 2
+                                  : ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   auto origin = [&](int b, int& m0_, int& n0_) {
-    if (g.sym) tri_origin<BM, BN>(g, b, m0_, n0_);
+    if (!RAG && g.sym) tri_origin<BM, BN>(g, b, m0_, n0_);
     else tile_origin<BM, BN>(g, b, m0_, n0_);
   };
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
   // split-K: this block covers slices [s0, s0 + nk) of every tile
-  const int nk = g.K / BKT / g.ksplit, s0 = blockIdx.y * nk;
+  const int slices = (g.K + BKT - 1) / BKT, per = (slices + g.ksplit - 1) / g.ksplit, s0 = blockIdx.y * per;
+  const int nk = min(per, slices - s0);  // at least 1: the launcher leaves no split empty
   const bool glu = BKM && EPI == EPI_SWIGLU_FWD;
   // this thread's byte offsets from a tile's slice origin
   uint32_t oa[PA], ob[PB];
@@ -816,14 +517,34 @@ gemm_dma_kernel(GemmArgs g) {
   typedef __attribute__((address_space(3))) bf16 lds_bf16;
   const uint32_t la0 = (uint32_t)(uintptr_t)(lds_bf16*)(S + wave * 512);
   const uint32_t lb0 = la0 + TA::ELEMS * 2;
+  // RAG: the ends of the operands, and this thread's k chunk within a slice (the same for all its
+  // loads: NW waves' loads are whole periods of the swizzle apart)
+  const bf16* ea = (const bf16*)g.A + (AK ? (int64_t)(g.M - 1) * g.lda + (g.a_padded ? g.lda : g.K)
+                                          : (int64_t)(g.K - 1) * g.lda + (g.a_padded ? g.lda : g.M));
+  const bf16* eb = (const bf16*)g.B + (BKM ? (int64_t)(glu ? 2 * g.glu - 1 : g.N - 1) * g.ldb + g.K
+                                           : (int64_t)(g.K - 1) * g.ldb + g.N);
+  int kca, kcb, r_;
+  static_assert(BKT == 64 && NW % 4 == 0, "one k chunk per thread");
+  TA::row_chunk(wave * 64 + lane, r_, kca);
+  TB::row_chunk(wave * 64 + lane, r_, kcb);
   auto issue = [&](const bf16* at, const bf16* bt, int s, int stage) {
     const bf16* as = at + s * step_a;
     const bf16* bs = bt + s * step_b;
     const uint32_t ta = la0 + stage * STAGE * 2, tb = lb0 + stage * STAGE * 2;
+    if constexpr (RAG) {
+      const u32x4 ra = buffer_range(as, ea), rb = buffer_range(bs, eb);
+      const int krem = g.K - (s0 + s) * BKT;
+      const bool outa = AK && 8 * kca >= krem, outb = BKM && 8 * kcb >= krem;
 #pragma unroll
-    for (int q = 0; q < PA; ++q) dma16(as, oa[q], ta + q * NW * 1024);
+      for (int q = 0; q < PA; ++q) dma16_range(ra, outa ? BUFFER_OUT : oa[q], ta + q * NW * 1024);
 #pragma unroll
-    for (int q = 0; q < PB; ++q) dma16(bs, ob[q], tb + q * NW * 1024);
+      for (int q = 0; q < PB; ++q) dma16_range(rb, outb ? BUFFER_OUT : ob[q], tb + q * NW * 1024);
+    } else {
+#pragma unroll
+      for (int q = 0; q < PA; ++q) dma16(as, oa[q], ta + q * NW * 1024);
+#pragma unroll
+      for (int q = 0; q < PB; ++q) dma16(bs, ob[q], tb + q * NW * 1024);
+    }
   };
 
   int t = blockIdx.x;
@@ -908,7 +629,7 @@ gemm_dma_kernel(GemmArgs g) {
     }
     wait_vm_lds<63>();
     block_barrier();
-    dma_epilogue<BM, BN, WM, WN, OutT, EPI, C_::RP>(g, acc, stg, m0, n0, wm0, wn0);
+    dma_epilogue<BM, BN, WM, WN, OutT, EPI, C_::RP, RAG>(g, acc, stg, m0, n0, wm0, wn0);
     if (!next) break;
     t = tn; m0 = m1; n0 = n1; at = atn; bt = btn;
   }
@@ -940,98 +661,91 @@ __global__ void __launch_bounds__(256) splitk_reduce(const float* __restrict__ w
   }
 }
 
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename OutT, bool CHECK>
-void launch_one(const GemmArgs& g, int nblk, hipStream_t st) {
-  using C_ = Cfg<BM, BN, WM, WN, AK, BKM>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, BN, WM, WN, AK, BKM, OutT, CHECK>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)C_::lds);
-    attr_set = true;
-  }
-  gemm_mfma_kernel<BM, BN, WM, WN, AK, BKM, OutT, CHECK><<<dim3(nblk, g.ksplit), C_::NT, C_::lds, st>>>(g);
-}
-
-template <int BM, int BN, int WM, int WN, typename OutT>
-void launch_cfg(const GemmArgs& g, hipStream_t st) {
-  const int nblk = (int)(cdiv(g.M, BM) * cdiv(g.N, BN));
-  // full tiles and whole k-slices everywhere (each split covers a whole number of slices)
-  const bool even = g.M % BM == 0 && g.N % BN == 0 && g.K % BK == 0 &&
-                    (g.ksplit == 1 || (g.K / BK) % g.ksplit == 0);
-#define L(AK, BKM)                                                                        \
-  do {                                                                                    \
-    if (even) launch_one<BM, BN, WM, WN, AK, BKM, OutT, false>(g, nblk, st);              \
-    else launch_one<BM, BN, WM, WN, AK, BKM, OutT, true>(g, nblk, st);                    \
-  } while (0)
-  if (g.a_kmajor && g.b_kmajor) L(true, true);
-  else if (g.a_kmajor) L(true, false);
-  else if (g.b_kmajor) L(false, true);
-  else L(false, false);
-#undef L
-}
-
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename OutT, int BKT, int NS, int EPI>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename OutT, int BKT, int NS, int EPI, bool RAG>
 void launch_dma_one(const GemmArgs& g, int nblk, hipStream_t st) {
   using C_ = DmaCfg<BM, BN, WM, WN, AK, BKM, BKT, NS>;
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)gemm_dma_kernel<BM, BN, WM, WN, AK, BKM, OutT, BKT, NS, EPI>,
+    (void)hipFuncSetAttribute((const void*)gemm_dma_kernel<BM, BN, WM, WN, AK, BKM, OutT, BKT, NS, EPI, RAG>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)C_::lds);
     attr_set = true;
   }
   // more tiles than the chip holds blocks at once: one block per slot, each walking its tiles
   int grid = nblk;
-  if (C_::persist && g.batch == 1 && g.K / BKT / g.ksplit >= NS - 1) {
+  if (C_::persist && g.batch == 1 && cdiv(g.K, BKT) / g.ksplit >= NS - 1) {
     const int per_cu = (int)(163840 / C_::lds);
     const int slots = (per_cu * device_cu_count() / g.ksplit) / 8 * 8;
     if (slots >= 8 && nblk > slots) grid = slots;
   }
-  gemm_dma_kernel<BM, BN, WM, WN, AK, BKM, OutT, BKT, NS, EPI><<<dim3(grid, g.ksplit, g.batch), C_::NT, C_::lds, st>>>(g);
+  gemm_dma_kernel<BM, BN, WM, WN, AK, BKM, OutT, BKT, NS, EPI, RAG>
+      <<<dim3(grid, g.ksplit, g.batch), C_::NT, C_::lds, st>>>(g);
 }
 
-// Direct-to-LDS variant: full tiles and whole slices per split only; false if the shape is not.
-// fp32 output: every operand layout, no fused epilogue; bf16 output: a k-contiguous A (every
-// bf16-output product of the stage has one) with each epilogue kind.
-template <int BM, int BN, int WM, int WN, typename OutT, int BKT, int NS>
+// Direct-to-LDS product of block tiles BM x BN; false if the kernels do not take the operand layouts
+// and the epilogue.  fp32 output: every operand layout, no fused epilogue; bf16 output: a
+// k-contiguous A (every bf16-output product of the stage has one) with each epilogue kind.
+template <int BM, int BN, int WM, int WN, typename OutT, int BKT, int NS, bool RAG>
 bool launch_dma_cfg(const GemmArgs& g, hipStream_t st) {
-  if (g.M % BM || g.N % BN || g.K % BKT || g.K == 0 || (g.K / BKT) % g.ksplit) return false;
-  if (g.sym && (BM != BN || g.M != g.N || g.epi != 0 || g.resid || sizeof(OutT) != 2)) return false;
-  const int nblk = g.sym ? (g.M / BM) * (g.M / BM + 1) / 2 : (g.M / BM) * (g.N / BN);
+  const int nblk = !RAG && g.sym ? (g.M / BM) * (g.M / BM + 1) / 2 : (int)(cdiv(g.M, BM) * cdiv(g.N, BN));
+#define L_(AK, BKM, E) launch_dma_one<BM, BN, WM, WN, AK, BKM, OutT, BKT, NS, E, RAG>(g, nblk, st)
   if constexpr (sizeof(OutT) == 4) {
-    if (g.a_kmajor && g.b_kmajor) launch_dma_one<BM, BN, WM, WN, true, true, OutT, BKT, NS, EPI_PLAIN>(g, nblk, st);
-    else if (g.a_kmajor) launch_dma_one<BM, BN, WM, WN, true, false, OutT, BKT, NS, EPI_PLAIN>(g, nblk, st);
-    else if (g.b_kmajor) launch_dma_one<BM, BN, WM, WN, false, true, OutT, BKT, NS, EPI_PLAIN>(g, nblk, st);
-    else launch_dma_one<BM, BN, WM, WN, false, false, OutT, BKT, NS, EPI_PLAIN>(g, nblk, st);
+    if (g.a_kmajor && g.b_kmajor) L_(true, true, EPI_PLAIN);
+    else if (g.a_kmajor) L_(true, false, EPI_PLAIN);
+    else if (g.b_kmajor) L_(false, true, EPI_PLAIN);
+    else L_(false, false, EPI_PLAIN);
   } else {
     if (!g.a_kmajor) return false;
     const int kind = g.epi != 0 ? g.epi : (g.resid ? EPI_RESID : EPI_PLAIN);
-#define K_(E)                                                                                     \
-  case E:                                                                                         \
-    if (g.b_kmajor) launch_dma_one<BM, BN, WM, WN, true, true, OutT, BKT, NS, E>(g, nblk, st);     \
-    else launch_dma_one<BM, BN, WM, WN, true, false, OutT, BKT, NS, E>(g, nblk, st);              \
+#define K_(E)                     \
+  case E:                         \
+    if (g.b_kmajor) L_(true, true, E); \
+    else L_(true, false, E);      \
     break;
     switch (kind) {
-      K_(EPI_PLAIN) K_(EPI_SWIGLU_BWD) K_(EPI_ROPE) K_(EPI_SWIGLU_FWD) K_(EPI_DELTA) K_(EPI_RESID)
-      K_(EPI_AXPBY) K_(EPI_AXPBY_DUP) K_(EPI_NS_SPLIT)
-      default: return false;
+      K_(EPI_PLAIN) K_(EPI_SWIGLU_BWD) K_(EPI_ROPE) K_(EPI_SWIGLU_FWD) K_(EPI_DELTA) K_(EPI_RESID) K_(EPI_AXPBY)
+      default:
+        if constexpr (!RAG) {  // the forms of whole tiles only
+          switch (kind) {
+            K_(EPI_AXPBY_DUP) K_(EPI_NS_SPLIT)
+            default: return false;
+          }
+        } else {
+          return false;
+        }
     }
 #undef K_
   }
+#undef L_
   return true;
 }
 
-}  // namespace
+template <int BM, int BN, int WM, int WN, bool RAG>
+bool launch_dma(const GemmArgs& g, hipStream_t st) {
+  return g.out_f32 ? launch_dma_cfg<BM, BN, WM, WN, float, BKT, 2, RAG>(g, st)
+                   : launch_dma_cfg<BM, BN, WM, WN, bf16, BKT, 2, RAG>(g, st);
+}
 
-namespace {
-// Tile choice for full tiles: 256 x 256 (8 waves of 64 x 128, 64-deep slices in 2 stages) when the
-// product has enough of them and is deep enough for the larger tile to pay (at K = 768 the
-// persistent 128 x 128 kernel is faster, from K = 1536 on the 256 x 256 one), else 128 x 128.
+// Tile choice: 256 x 256 (8 waves of 64 x 128, 64-deep slices in 2 stages) when the product has
+// enough of them and is deep enough for the larger tile to pay (at K = 768 the persistent
+// 128 x 128 kernel is faster, from K = 1536 on the 256 x 256 one), else 128 x 128.
 constexpr int BIG_K = 1536;
 bool use_big(const GemmArgs& g) {
   const int64_t t256 = cdiv(g.M, 256) * cdiv(g.N, 256);
-  return g.M % 256 == 0 && g.N % 256 == 0 && g.K % 64 == 0 && g.K >= BIG_K &&
-         (t256 >= 512 || (t256 >= 256 && g.K >= 2048));
+  return g.K >= BIG_K && (t256 >= 512 || (t256 >= 256 && g.K >= 2048));
 }
+
+// What every direct-to-LDS kernel needs: 16-byte aligned operand rows (a k-contiguous operand of
+// whole 8-element chunks, or zero-padded rows; a row-contiguous one of whole chunks of rows), 16-byte
+// output rows for bf16 output, and tile offsets below 2^31 bytes.
+bool dma_operands(const GemmArgs& g) {
+  if (g.K <= 0 || g.lda % 8 || g.ldb % 8) return false;
+  if ((uintptr_t)g.A % 16 || (uintptr_t)g.B % 16 || (uintptr_t)g.C % 16) return false;
+  if (!g.a_padded && (g.a_kmajor ? g.K : g.M) % 8) return false;
+  if ((g.b_kmajor ? g.K : g.N) % 8) return false;
+  if (!g.out_f32 && (g.N % 8 || g.ldc % 8)) return false;
+  return 256 * (int64_t)std::max(g.lda, g.ldb) + (int64_t)g.glu * g.ldb < ((int64_t)1 << 30);
+}
+
 }  // namespace
 
 int device_cu_count() {
@@ -1047,82 +761,65 @@ int device_cu_count() {
 }
 
 bool gemm_mfma_try(const GemmArgs& g0, hipStream_t st) {
-  // vector-load alignment: 8 elements along every contiguous dimension, rows in groups of 4
-  if (g0.K % 8 || g0.M % 8 || g0.N % 8 || g0.lda % 8 || g0.ldb % 8 || g0.ldc % 8) return false;
-  if (g0.batch > 1 || g0.sym || g0.epi == EPI_AXPBY || g0.epi == EPI_AXPBY_DUP || g0.epi == EPI_NS_SPLIT) {
-    // batched and AXPBY products run on the direct-to-LDS kernels only (full tiles, 16-byte
-    // aligned operands and batch strides; AXPBY with bf16 output, fp32 output plain or
-    // accumulating beta C); the caller loops over the others
-    const bool ok = g0.a_kmajor && g0.M % 128 == 0 && g0.N % 128 == 0 && g0.K % 64 == 0 &&
-                    (g0.epi == 0 || ((g0.epi == EPI_AXPBY || g0.epi == EPI_AXPBY_DUP || g0.epi == EPI_NS_SPLIT) &&
-                                     !g0.out_f32)) && !g0.resid &&
-                    ((uintptr_t)g0.A | (uintptr_t)g0.B | (uintptr_t)g0.C | (uintptr_t)g0.D) % 16 == 0 &&
-                    (g0.sA | g0.sB | g0.sC | g0.sD) % 8 == 0 &&
-                    (!g0.sym || (g0.M == g0.N && g0.epi == 0 && !g0.out_f32));
-    if (!ok) return false;
-    GemmArgs g = g0;
-    g.ksplit = 1;
-    return g.out_f32 ? launch_dma_cfg<128, 128, 64, 64, float, 64, 2>(g, st)
-                     : launch_dma_cfg<128, 128, 64, 64, bf16, 64, 2>(g, st);
+  if (!dma_operands(g0)) return false;
+  GemmArgs g = g0;
+  g.ksplit = 1;
+  if (g.batch > 1 || g.sym || g.epi == EPI_AXPBY || g.epi == EPI_AXPBY_DUP || g.epi == EPI_NS_SPLIT) {
+    // batched, symmetric and AXPBY products (a k-contiguous A; AXPBY with bf16 output, fp32 output
+    // plain or accumulating beta C; 16-byte aligned batch strides)
+    if (!g.a_kmajor || g.resid || (g.epi != 0 && (g.epi < EPI_AXPBY || g.out_f32)) || (uintptr_t)g.D % 16 ||
+        (g.sA | g.sB | g.sC | g.sD) % 8 || (g.out_f32 && (g.N | g.ldc) % 4))
+      return false;
+    if (g.sym && (g.M != g.N || g.epi != 0 || g.out_f32)) return false;
+    if (gemm_batched_tiles(g.M, g.N, g.K)) return launch_dma<128, 128, 64, 64, false>(g, st);
+    return launch_dma<128, 128, 64, 64, true>(g, st);  // every tile of a symmetric product
   }
-  if (g0.epi == 3) {
-    // the SwiGLU forward rides in the epilogue of the direct-to-LDS kernels only (their B loader
-    // gathers gate and up rows); any other shape runs the product, then the SwiGLU kernel
-    const bool fused = !g0.out_f32 && g0.b_kmajor && g0.K > 0 && g0.K % 64 == 0 && g0.M % 128 == 0 &&
-                       g0.N == 2 * g0.glu && g0.glu % 64 == 0 && g0.ld_out2 % 8 == 0 &&
-                       (uintptr_t)g0.out2 % 16 == 0;
+  if (g.epi == 3) {
+    // the SwiGLU forward rides in the epilogue (the B loader gathers gate and up rows) when the
+    // panels are whole; any other shape runs the product, then the SwiGLU kernel
+    const bool fused = !g.out_f32 && g.b_kmajor && g.N == 2 * g.glu && g.glu % 64 == 0 && g.ld_out2 % 8 == 0 &&
+                       (uintptr_t)g.out2 % 16 == 0;
     if (!fused) {
-      GemmArgs p = g0;
+      GemmArgs p = g;
       p.epi = 0;
       p.glu = 0;
       if (!gemm_mfma_try(p, st)) return false;
-      launch_swiglu_fwd(true, g0.C, g0.out2, g0.M, g0.glu, st);
+      launch_swiglu_fwd(true, g.C, g.out2, g.M, g.glu, st);
       return true;
     }
   }
-  if (g0.epi == 1 && (g0.out_f32 || g0.ld_aux % 8 || (uintptr_t)g0.aux % 16)) return false;
-  if ((uintptr_t)g0.A % 16 || (uintptr_t)g0.B % 16 || (uintptr_t)g0.C % 16 || (uintptr_t)g0.resid % 16)
-    return false;
-  if (g0.epi == 4) {
-    // delta rides in the epilogue of the direct-to-LDS kernels when a wave's columns hold whole
-    // heads (every lane of the epilogue active); otherwise the caller computes it separately
-    const bool full = !g0.out_f32 && g0.K > 0 && g0.K % 64 == 0 && g0.M % 128 == 0 && g0.N % 128 == 0;
-    const int wn = full && use_big(g0) ? 128 : 64;
-    if (!full || g0.delta_hd < 8 || wn % g0.delta_hd || g0.ld_aux % 8 || (uintptr_t)g0.aux % 16) return false;
-  }
-  GemmArgs g = g0;
-  g.ksplit = 1;
-  const int64_t mn = (int64_t)g.M * g.N;
-  // Full tiles go to the direct-to-LDS kernels (use_big picks 256 x 256 or 128 x 128: 4 waves,
-  // 64-deep slices in 2 stages, two blocks per CU, persistent when the tiles outnumber the
-  // blocks the chip holds); ragged shapes to the register-staged kernel with bounds-checked loads.
-  constexpr int DKB = 64, DKS = 64;
-  const bool full128 = g.M % 128 == 0 && g.N % 128 == 0 && g.K % DKS == 0;
-  const int64_t t256 = cdiv(g.M, 256) * cdiv(g.N, 256), t128 = cdiv(g.M, 128) * cdiv(g.N, 128);
+  if (g.epi == 1 && (g.out_f32 || g.ld_aux % 8 || (uintptr_t)g.aux % 16)) return false;
+  if ((uintptr_t)g.resid % 16) return false;
   const bool big = use_big(g);
-  const int64_t tiles = big ? t256 : t128;
+  const int wn = big ? 128 : 64;  // columns of one wave
+  // delta rides in the epilogue when a wave's columns hold whole heads; otherwise the caller
+  // computes it separately
+  if (g.epi == 4 && (g.out_f32 || g.delta_hd < 8 || wn % g.delta_hd || g.N % g.delta_hd || g.ld_aux % 8 ||
+                     (uintptr_t)g.aux % 16))
+    return false;
+  const int64_t mn = (int64_t)g.M * g.N;
+  const int64_t tiles = big ? cdiv(g.M, 256) * cdiv(g.N, 256) : cdiv(g.M, 128) * cdiv(g.N, 128);
+  const int64_t slices = cdiv(g.K, BKT);
   if (g.out_f32 && g.ws && g.ldc == g.N && tiles < 512 && g.K >= 2048) {
-    // deterministic split-K for underfilled fp32-output products: whole slices per split
-    const int kq = big ? DKB : (full128 ? DKS : BK);
+    // deterministic split-K for underfilled fp32-output products: whole slices per split, equal
+    // splits where K is a whole number of slices, none empty otherwise
     int s = (int)std::min<int64_t>(8, cdiv(512, tiles));
-    while (s > 1 && (s * mn > g.ws_elems || g.K / s < 512 || (g.K / kq) % s)) --s;
+    while (s > 1 && (s * mn > g.ws_elems || g.K / s < 512 ||
+                     (g.K % BKT == 0 ? slices % s != 0 : (s - 1) * cdiv(slices, s) >= slices)))
+      --s;
     g.ksplit = s;
   }
   // RoPE in the epilogue needs every head whole inside one wave's columns
-  const int wn = big ? 128 : 64;
   const bool rope_after = g.epi == 2 && (g.out_f32 || wn % g.rope_hd != 0);
   if (rope_after) g.epi = 0;
-  bool done = false;  // the direct-to-LDS launchers decline shapes they do not take (K = 0)
-  if (big)
-    done = g.out_f32 ? launch_dma_cfg<256, 256, 64, 128, float, DKB, 2>(g, st)
-                     : launch_dma_cfg<256, 256, 64, 128, bf16, DKB, 2>(g, st);
-  else if (full128)
-    done = g.out_f32 ? launch_dma_cfg<128, 128, 64, 64, float, DKS, 2>(g, st)
-                     : launch_dma_cfg<128, 128, 64, 64, bf16, DKS, 2>(g, st);
-  if (!done) {
-    if (g.out_f32) launch_cfg<128, 128, 64, 64, float>(g, st);
-    else launch_cfg<128, 128, 64, 64, bf16>(g, st);
-  }
+  // whole tiles and slices (and equal splits): the loads and stores need no range
+  const int bm = big ? 256 : 128;
+  const bool whole = g.M % bm == 0 && g.N % bm == 0 && g.K % BKT == 0 && slices % g.ksplit == 0 &&
+                     (g.N | g.ldc) % 4 == 0;
+  bool done;
+  if (big) done = whole ? launch_dma<256, 256, 64, 128, false>(g, st) : launch_dma<256, 256, 64, 128, true>(g, st);
+  else done = whole ? launch_dma<128, 128, 64, 64, false>(g, st) : launch_dma<128, 128, 64, 64, true>(g, st);
+  if (!done) return false;
   if (g.ksplit > 1)
     splitk_reduce<<<(unsigned)cdiv(cdiv(mn, 4), 256), 256, 0, st>>>(g.ws, g.ksplit, mn, (float*)g.C, g.beta);
   if (rope_after)

@@ -80,12 +80,13 @@ void launch_embed_scatter(bool bf, const void* dx0, const uint32_t* sorted_pos,
                           const int32_t* row_start, int vocab, int d, float* de, bool accumulate,
                           hipStream_t st);
 // cross-entropy rows of fp32 logits [rows, vocab]: the forward writes lse and the row loss
-// lse - z[target]; the backward dlogits = (exp(z - lse) - onehot) * scale (bf16/fp32).  Targets
+// lse - z[target]; the backward dlogits = (exp(z - lse) - onehot) * scale (bf16/fp32, rows of ld
+// elements: ld - vocab < 256 zeros after the vocab values; ld a multiple of 4).  Targets
 // outside [0, vocab) give zero loss and zero gradient.
 void launch_ce_fwd(const float* logits, const int32_t* targets, int rows, int vocab, float* lse,
                    float* row_loss, hipStream_t st);
 void launch_ce_bwd(bool bf, const float* logits, const int32_t* targets, const float* lse, int rows, int vocab,
-                   float scale, void* dlogits, hipStream_t st);
+                   float scale, void* dlogits, int ld, hipStream_t st);
 void launch_mean(const float* v, int n, float* out, hipStream_t st);
 
 // ------------------------------------------------------------------ GEMM (gemm.hip)
@@ -98,6 +99,9 @@ void launch_mean(const float* v, int n, float* out, hipStream_t st);
 struct GemmArgs {
   int M, N, K;
   const void* A; int lda; bool a_kmajor;
+  // A's rows are allocated to lda elements (a multiple of 8) and hold zeros past the operand's
+  // edge: K of a k-contiguous A, or M of a row-contiguous one, may then be any number
+  bool a_padded = false;
   const void* B; int ldb; bool b_kmajor;
   void* C; int ldc; bool out_f32; float beta;
   const void* resid;
@@ -129,8 +133,8 @@ struct GemmArgs {
   int batch = 1;
   int64_t sA = 0, sB = 0, sC = 0, sD = 0;
   // sym: the product is symmetric (M == N, plain bf16 output): the direct-to-LDS kernels compute
-  // the tiles on and above the diagonal only and write each off-diagonal one also transposed; the
-  // other kernels ignore the flag (and compute every tile)
+  // the tiles on and above the diagonal only and write each off-diagonal one also transposed; a
+  // product of partial tiles ignores the flag (and computes every tile)
   int sym = 0;
 };
 constexpr int GEMM_EPI_AXPBY = 6;

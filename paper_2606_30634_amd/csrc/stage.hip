@@ -121,7 +121,7 @@ struct stage {
   hipEvent_t ev_m2s = nullptr, ev_wjoin = nullptr, ev_wg[5] = {};
   bool bf;
   size_t esz;  // bytes per compute element
-  int T, qkvw, hqd;
+  int T, qkvw, hqd, lddlog = 0;
   // flat parameter layout
   int64_t n_flat = 0, off_embed = -1, off_final = -1, off_head = -1;  // off_head = off_embed when tied
   std::vector<BlockOff> boff;
@@ -404,7 +404,10 @@ size_t layout(stage* S, char* base) {
   S->cos_t = (float*)carve((int64_t)sh.seq_len * (hd / 2) * 4);
   S->sin_t = (float*)carve((int64_t)sh.seq_len * (hd / 2) * 4);
   S->sort_ws = sh.first_stage ? (int32_t*)carve(token_sort_ws_elems((int)T) * 4) : nullptr;
-  S->dlog = sh.last_stage ? carve(T * (int64_t)sh.vocab * esz) : nullptr;
+  // rows of whole 16-byte chunks for any vocabulary (zeros past it), so that the head's products
+  // read them as vectors
+  S->lddlog = (sh.vocab + 7) / 8 * 8;
+  S->dlog = sh.last_stage ? carve(T * S->lddlog * esz) : nullptr;
   S->dhf = sh.last_stage ? carve(T * d * esz) : nullptr;
   S->row_loss = sh.last_stage ? (float*)carve(T * 4) : nullptr;
   // Muon: every block's wq, wk, wv, wo, wgate, wup, wdown; a group per wide-orientation shape
@@ -902,12 +905,15 @@ int stage_backward(stage_t* s, int32_t slot, const void* dy, void* dx_out, int32
   bool head_wrote_embed = false;
   if (sh.last_stage) {
     launch_ce_bwd(bf, sl.logits, sl.targets, sl.lse_ce, T, sh.vocab, 1.0f / ((float)T * microbatches_per_step),
-                  s->dlog, st);
+                  s->dlog, s->lddlog, st);
     // dhf = dlogits W ; dW (+)= dlogits^T hf   (W the head matrix, or the tied embedding)
-    run_gemm(s, gemm(T, d, sh.vocab, s->dlog, sh.vocab, true, s->wptr(vi, s->off_head), d, false,
-                         s->dhf, d));
-    run_wgrad(s, gemm(sh.vocab, d, T, s->dlog, sh.vocab, false, sl.hf, d, false, g + s->off_head, d,
-                          true, first ? 0.f : 1.f), WG_HEAD);
+    GemmArgs gd = gemm(T, d, sh.vocab, s->dlog, s->lddlog, true, s->wptr(vi, s->off_head), d, false, s->dhf, d);
+    gd.a_padded = true;
+    run_gemm(s, gd);
+    GemmArgs gw = gemm(sh.vocab, d, T, s->dlog, s->lddlog, false, sl.hf, d, false, g + s->off_head, d, true,
+                       first ? 0.f : 1.f);
+    gw.a_padded = true;
+    run_wgrad(s, gw, WG_HEAD);
     head_wrote_embed = s->off_head == s->off_embed;
     const int np = launch_rmsnorm_bwd(bf, s->dhf, sl.y, sl.rstdf, s->wptr(vi, s->off_final), nullptr, s->dA,
                                        s->rms_part, T, d, st);
