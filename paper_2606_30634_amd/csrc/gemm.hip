@@ -1,15 +1,17 @@
 // GEMM entry: C[m, n] (+)= sum_k A(m, k) B(n, k) for the three products of a linear layer without
 // bias (forward y = x W^T, input gradient dx = dy W, weight gradient dW = dy^T x).
 //
-// This file holds the reference tiling used for fp32 workloads and for shapes the MFMA kernel
-// does not take: 64x64 output tile, 16-deep k slices staged through LDS, 4x4 outputs per
-// thread, fp32 FMA.  bf16 workloads go to the MFMA kernel in gemm_mfma.hip.
+// bf16 products go to the MFMA kernels in gemm_mfma.hip, fp32 ones to those in gemm_f32.hip.  This
+// file holds the reference tiling for bf16 operands that the MFMA kernels do not take (a caller's
+// gradient that does not start on 16 bytes): 64x64 output tile, 16-deep k slices staged through LDS,
+// 4x4 outputs per thread, fp32 FMA.
 #include "common.h"
 #include "kernels.h"
 #include <cstdio>
 #include <cstdlib>
 
-bool gemm_mfma_try(const GemmArgs& g, hipStream_t st);  // gemm_mfma.hip
+bool gemm_mfma_try(const GemmArgs& g, hipStream_t st);   // gemm_mfma.hip
+void launch_gemm_f32(const GemmArgs& g, hipStream_t st);  // gemm_f32.hip
 
 namespace {
 
@@ -99,13 +101,9 @@ void launch_layout(const GemmArgs& g, hipStream_t st) {
 
 }  // namespace
 
-void launch_gemm_tiled(bool bf, const GemmArgs& g, hipStream_t st) {
-  if (bf) {
-    if (g.out_f32) launch_layout<bf16, float>(g, st);
-    else launch_layout<bf16, bf16>(g, st);
-  } else {
-    launch_layout<float, float>(g, st);
-  }
+void launch_gemm_tiled(const GemmArgs& g, hipStream_t st) {
+  if (g.out_f32) launch_layout<bf16, float>(g, st);
+  else launch_layout<bf16, bf16>(g, st);
 }
 
 // y = alpha y + beta x, one thread per element of a rows x cols block of row stride ld
@@ -128,6 +126,10 @@ void launch_axpby(bool bf, void* y, const void* x, float alpha, float beta, int 
 void launch_gemm(bool bf, const GemmArgs& g, hipStream_t st) {
   if (g.M == 0 || g.N == 0) return;
   if (bf && gemm_mfma_try(g, st)) return;
+  if (!bf && g.epi != 4) {
+    launch_gemm_f32(g, st);
+    return;
+  }
   if (g.epi == GEMM_EPI_AXPBY_DUP || g.epi == GEMM_EPI_NS_SPLIT) {
     // only the batched direct-to-LDS kernels implement these; callers check gemm_batched_tiles()
     fprintf(stderr, "launch_gemm: epilogue %d needs whole tiles and bf16 operands\n", g.epi);
@@ -168,17 +170,17 @@ void launch_gemm(bool bf, const GemmArgs& g, hipStream_t st) {
     GemmArgs p = g;
     p.epi = 0;
     p.glu = 0;
-    launch_gemm_tiled(bf, p, st);
+    launch_gemm_tiled(p, st);
     launch_swiglu_fwd(bf, g.C, g.out2, g.M, g.glu, st);
     return;
   }
   if (g.epi == 2) {  // the reference tiling writes the products, then the rotation runs
     GemmArgs p = g;
     p.epi = 0;
-    launch_gemm_tiled(bf, p, st);
+    launch_gemm_tiled(p, st);
     launch_rope(bf, g.C, g.M, g.rope_S, g.rope_cols / g.rope_hd, g.rope_hd, g.ldc, g.rope_cos, g.rope_sin,
                 false, st);
     return;
   }
-  launch_gemm_tiled(bf, g, st);
+  launch_gemm_tiled(g, st);
 }
