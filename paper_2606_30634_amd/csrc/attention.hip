@@ -1,11 +1,22 @@
-// Causal grouped-query attention (App. E.2), reference tiling: one thread per query (forward,
-// dQ) or key (dK, dV) row, K/V (or Q/dO) tiles of 64 rows staged through LDS, online softmax in
-// fp32.  Used for fp32 workloads and shapes the MFMA kernels (attention_mfma.hip) do not take.
+// Causal grouped-query attention (App. E.2) in fp32 on the matrix cores, for the fp32 stage and for
+// the bf16 stage's head dimensions that attention_mfma.hip does not take (bf16 in and out there).
 //
 //   S = q k^T / sqrt(hd) on j <= i;  P = softmax(S);  o = P v;  lse_i = log sum_j exp(S_ij)
 //   delta_i = sum_c dO_ic O_ic;  dP = dO v^T;  dS = P (dP - delta);  dq = dS k / sqrt(hd)
 //   dk = dS^T q / sqrt(hd) and dv = P^T dO, summed over the query heads of a key/value head.
 // Query head h reads key/value head h / (Hq / Hkv).
+//
+// v_mfma_f32_32x32x2_f32 throughout (lane l: operand row l mod 32 at k = l / 32; accumulator e of
+// lane l: row 8 (e / 4) + 4 (l / 32) + e mod 4, column l mod 32).  A block of 4 waves owns 32 rows
+// (queries for o and dq, keys for dk and dv) of one head; its waves take every fourth 32-row tile of
+// the other side and their sums meet in LDS, in wave order, at the end: the sequences here are short,
+// so it is the serial chain of one row block, not the chip's rate, that bounds a launch.  Scores are
+// formed with the block's rows as columns (S^T = K Q^T; S = Q K^T for dk, dv), so accumulator e of a
+// lane pair holds two rows 4 apart of the other side and is itself the k = 2 operand of the next
+// product: no value moves between lanes.  Operands come from global memory (L2) straight into
+// registers: an MFMA takes 64 cycles, a lane's loads for it at most 2.
+// At 4 sequences of 256, 8 heads of 64: forward 247 -> 17 us, backward 690 -> 51 us (delta, rotation,
+// dq, dk and dv; one thread per row in five launches before).
 #include "common.h"
 #include "kernels.h"
 
@@ -15,11 +26,123 @@ bool attention_mfma_delta_try(const AttnArgs& a, hipStream_t st);
 
 namespace {
 
-constexpr int TR = 64;  // rows per block and per LDS tile
+constexpr int TR = 32;  // rows of a block and of a tile
+constexpr int NW = 4;   // waves of a block
+
+__device__ __forceinline__ f32x16 mfma2(float a, float b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// Four consecutive elements as fp32 (rows start on 4 elements: head_dim and every width are
+// multiples of 32)
+__device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 ld4(const bf16* p) {
+  const bf16x4 v = *reinterpret_cast<const bf16x4*>(p);
+  return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+}
+__device__ __forceinline__ void st4(float* p, const f32x4& v) { *reinterpret_cast<f32x4*>(p) = v; }
+__device__ __forceinline__ void st4(bf16* p, const f32x4& v) {
+  *reinterpret_cast<bf16x4*>(p) = bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
+}
+
+// Row operand: this lane's half of row `row` (stride ld) for a contraction over the head dimension:
+// group q holds elements 8 q + 4 (lane / 32) .. + 3, so that step (q, j) pairs 8 q + j with 8 q + 4 + j.
+template <int HD>
+struct RowFrag {
+  f32x4 v[HD / 8];
+  template <typename T>
+  __device__ __forceinline__ void load(const T* p, int64_t row, int ld) {
+    const T* r = p + row * ld + 4 * (threadIdx.x % 64 / 32);
+#pragma unroll
+    for (int q = 0; q < HD / 8; ++q) v[q] = ld4(r + 8 * q);
+  }
+};
+// S (+)= A B^T over the head dimension: accumulator rows are A's rows, columns B's
+template <int HD>
+__device__ __forceinline__ f32x16 rows_product(const RowFrag<HD>& a, const RowFrag<HD>& b) {
+  f32x16 s;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+  for (int q = 0; q < HD / 8; ++q)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s = mfma2(a.v[q][j], b.v[q][j], s);
+  return s;
+}
+
+// acc[dt] (rows 32 dt .. of X^T, columns the block's rows) += X^T W over the 32 tile rows of X, whose
+// weights w sit in an accumulator (rows: tile rows).  Tile row r is row min(row0 + r, last) of X.
+template <int HD, typename T>
+__device__ __forceinline__ void cols_product(f32x16 (&acc)[HD / 32], const T* x, int row0, int last, int ld,
+                                             const f32x16& w) {
+  const int lane = threadIdx.x % 64;
+  float f[HD / 32][16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const T* r = x + (int64_t)min(row0 + 8 * (e / 4) + 4 * (lane / 32) + e % 4, last) * ld + lane % 32;
+#pragma unroll
+    for (int dt = 0; dt < HD / 32; ++dt) f[dt][e] = to_f32(r[32 * dt]);
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+#pragma unroll
+    for (int dt = 0; dt < HD / 32; ++dt) acc[dt] = mfma2(f[dt][e], w[e], acc[dt]);
+}
+
+// Sum of the waves' accumulators over red ([wave][dt][e][lane]), in wave order.
+template <int HD>
+__device__ __forceinline__ void put_partial(float* red, const f32x16 (&acc)[HD / 32], float scale) {
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+#pragma unroll
+  for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[((wave * (HD / 32) + dt) * 16 + e) * 64 + lane] = acc[dt][e] * scale;
+}
+template <int HD>
+__device__ __forceinline__ float get_sum(const float* red, int dt, int e) {
+  const int lane = threadIdx.x % 64;
+  float v = red[(dt * 16 + e) * 64 + lane];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) v += red[((w * (HD / 32) + dt) * 16 + e) * 64 + lane];
+  return v;
+}
+
+// The summed rows leave as rows of out (row row0 + lane mod 32, elements 32 dt + 8 (e / 4) + 4 (lane /
+// 32) ..+ 3: 16-byte chunks): wave w writes the chunks e / 4 = w.  With RoPE tables the rows are
+// rotated back by -angle(position) first: element c < hd/2 pairs with c + hd/2, which the same lane
+// holds (another dt, or for head dimension 32 e + 8).
+template <int HD, typename T>
+__device__ __forceinline__ void store_rows(const float* red, float scale, T* out, int ld, int row0, int S,
+                                           const float* cos_t, const float* sin_t, float* out32 = nullptr) {
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int row = row0 + lane % 32;
+#pragma unroll
+  for (int dt = 0; dt < HD / 32; ++dt) {
+    const int c = 32 * dt + 8 * wave + 4 * (lane / 32);
+    f32x4 v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = get_sum<HD>(red, dt, 4 * wave + j) * scale;
+    if (cos_t) {
+      constexpr int HH = HD / 2;
+      const bool first = c < HH;
+      const int pd = HD == 32 ? dt : (first ? dt + HD / 64 : dt - HD / 64), pe = HD == 32 ? (4 * wave) ^ 8 : 4 * wave;
+      const int64_t t = (int64_t)min(row, S - 1) * HH + c % HH;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float p = get_sum<HD>(red, pd, pe + j) * scale, cs = cos_t[t + j], sn = sin_t[t + j];
+        v[j] = first ? v[j] * cs + p * sn : v[j] * cs - p * sn;
+      }
+    }
+    if (row < S) {
+      st4(out + (int64_t)row * ld + c, v);
+      if (out32) st4(out32 + (int64_t)row * ld + c, v);
+    }
+  }
+}
 
 struct Geo {
   int ld, koff, voff, group;
-  __device__ Geo(const AttnArgs& a) {
+  __device__ explicit Geo(const AttnArgs& a) {
     ld = (a.Hq + 2 * a.Hkv) * a.hd;
     koff = a.Hq * a.hd;
     voff = (a.Hq + a.Hkv) * a.hd;
@@ -27,249 +150,235 @@ struct Geo {
   }
 };
 
+__device__ __forceinline__ float pair_max(float v) { return fmaxf(v, __shfl_xor(v, 32, WAVE)); }
+__device__ __forceinline__ float pair_sum(float v) { return v + __shfl_xor(v, 32, WAVE); }
+
+// One block per (32 queries, query head, sequence); longest causal ranges first.
 template <typename T, int HD>
-__global__ void __launch_bounds__(TR) attn_fwd(AttnArgs a) {
-  __shared__ float Ks[TR][HD];
-  __shared__ float Vs[TR][HD];
+__global__ void __launch_bounds__(NW * 64) attn_fwd(AttnArgs a) {
+  __shared__ float red[NW * (HD / 32) * 16 * 64];
+  float (*stat)[NW][TR] = reinterpret_cast<float (*)[NW][TR]>(red);  // [2], before the partial sums
   const Geo g(a);
   const int b = blockIdx.z, h = blockIdx.y, kvh = h / g.group;
-  const int i = blockIdx.x * TR + threadIdx.x;
-  const T* qkv = (const T*)a.qkv;
+  const int q0 = (gridDim.x - 1 - blockIdx.x) * TR;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, q = q0 + lane % 32;
+  const T* qkv = (const T*)a.qkv + (int64_t)b * a.S * g.ld;
+  const T* kp = qkv + g.koff + kvh * HD;
+  const T* vp = qkv + g.voff + kvh * HD;
   const float scale = 1.0f / sqrtf((float)HD);
-  float q[HD], o[HD];
-  const int64_t rowq = (int64_t)(b * a.S + min(i, a.S - 1)) * g.ld;
+  RowFrag<HD> qf;
+  qf.load(qkv + h * HD, min(q, a.S - 1), g.ld);
 #pragma unroll
-  for (int c = 0; c < HD; ++c) { q[c] = to_f32(qkv[rowq + h * HD + c]) * scale; o[c] = 0.f; }
+  for (int i = 0; i < HD / 8; ++i) qf.v[i] *= scale;
+  f32x16 o[HD / 32];
+#pragma unroll
+  for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
   float m = -INFINITY, l = 0.f;
-  const int last = min(a.S - 1, blockIdx.x * TR + TR - 1);
-  for (int j0 = 0; j0 <= last; j0 += TR) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < TR * HD; e += TR) {
-      const int r = e / HD, c = e % HD, j = j0 + r;
-      const int64_t row = (int64_t)(b * a.S + min(j, a.S - 1)) * g.ld;
-      Ks[r][c] = to_f32(qkv[row + g.koff + kvh * HD + c]);
-      Vs[r][c] = to_f32(qkv[row + g.voff + kvh * HD + c]);
+  for (int k0 = wave * TR; k0 <= q0; k0 += NW * TR) {
+    RowFrag<HD> kf;
+    kf.load(kp, min(k0 + lane % 32, a.S - 1), g.ld);
+    f32x16 s = rows_product<HD>(kf, qf);  // rows: keys; column: this lane's query
+    float mt = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      if (k0 + 8 * (e / 4) + 4 * (lane / 32) + e % 4 > q) s[e] = -INFINITY;
+      mt = fmaxf(mt, s[e]);
     }
-    __syncthreads();
-    const int jend = min(TR, i - j0 + 1);
-    for (int r = 0; r < jend; ++r) {
-      float s = 0.f;
+    const float mn = fmaxf(m, pair_max(mt));  // finite: key k0 <= q0 is visible to every query
+    const float corr = expf(m - mn);          // 0 for the first tile
+    float rs = 0.f;
 #pragma unroll
-      for (int c = 0; c < HD; ++c) s += q[c] * Ks[r][c];
-      if (s > m) {
-        const float corr = expf(m - s);
-        l *= corr;
-#pragma unroll
-        for (int c = 0; c < HD; ++c) o[c] *= corr;
-        m = s;
-      }
-      const float p = expf(s - m);
-      l += p;
-#pragma unroll
-      for (int c = 0; c < HD; ++c) o[c] += p * Vs[r][c];
+    for (int e = 0; e < 16; ++e) {
+      s[e] = expf(s[e] - mn);
+      rs += s[e];
     }
+    l = l * corr + pair_sum(rs);
+    m = mn;
+#pragma unroll
+    for (int dt = 0; dt < HD / 32; ++dt) o[dt] *= corr;
+    cols_product<HD>(o, vp, k0, a.S - 1, g.ld, s);
   }
-  if (i >= a.S) return;
-  T* out = (T*)a.o;
-  const int64_t rowo = (int64_t)(b * a.S + i) * a.Hq * HD + h * HD;
-  const float inv = 1.0f / l;
+  // the waves' statistics: o = sum_w e^(m_w - M) o_w / sum_w e^(m_w - M) l_w (wave 0 always has a tile)
+  if (lane < TR) {
+    stat[0][wave][lane] = m;
+    stat[1][wave][lane] = l;
+  }
+  __syncthreads();
+  float M = -INFINITY, L = 0.f;
 #pragma unroll
-  for (int c = 0; c < HD; ++c) out[rowo + c] = from_f32<T>(o[c] * inv);
-  if (a.o32)
-    for (int c = 0; c < HD; ++c) a.o32[rowo + c] = o[c] * inv;
-  a.lse[((int64_t)b * a.Hq + h) * a.S + i] = m + logf(l);
+  for (int w = 0; w < NW; ++w) M = fmaxf(M, stat[0][w][lane % 32]);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) L += expf(stat[0][w][lane % 32] - M) * stat[1][w][lane % 32];
+  __syncthreads();
+  put_partial<HD>(red, o, expf(m - M) / L);
+  __syncthreads();
+  store_rows<HD>(red, 1.0f, (T*)a.o + (int64_t)b * a.S * a.Hq * HD + h * HD, a.Hq * HD, q0, a.S, nullptr, nullptr,
+                 sizeof(T) == 2 && a.o32 ? a.o32 + (int64_t)b * a.S * a.Hq * HD + h * HD : nullptr);
+  if (wave == 0 && lane < TR && q < a.S) a.lse[((int64_t)b * a.Hq + h) * a.S + q] = M + logf(L);
 }
 
-// delta_i = sum_c dO_ic O_ic  (per query row and head)
+// delta_i = sum_c dO_ic O_ic per (batch, head, query): HD / 4 lanes per row
 template <typename T, int HD>
 __global__ void __launch_bounds__(256) attn_delta(AttnArgs a) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (b, h, i)
-  if (idx >= (int64_t)a.B * a.Hq * a.S) return;
-  const int i = idx % a.S, h = (idx / a.S) % a.Hq, b = idx / ((int64_t)a.S * a.Hq);
-  const int64_t r = (int64_t)(b * a.S + i) * a.Hq * HD + h * HD;
-  const T* dO = (const T*)a.dout;
+  constexpr int LR = HD / 4;
+  const int64_t r = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LR;  // (b, i, h) in memory order
+  const int c = (threadIdx.x % LR) * 4;
   float s = 0.f;
-  if (a.o32) {
-    for (int c = 0; c < HD; ++c) s += a.o32[r + c] * to_f32(dO[r + c]);
-  } else {
-    const T* O = (const T*)a.o;
-    for (int c = 0; c < HD; ++c) s += to_f32(O[r + c]) * to_f32(dO[r + c]);
+  const bool in = r < (int64_t)a.B * a.S * a.Hq;
+  if (in) {
+    const f32x4 d = ld4((const T*)a.dout + r * HD + c);
+    const f32x4 o = sizeof(T) == 2 && a.o32 ? ld4(a.o32 + r * HD + c) : ld4((const T*)a.o + r * HD + c);
+    s = (o[0] * d[0] + o[1] * d[1]) + (o[2] * d[2] + o[3] * d[3]);
   }
-  a.delta[idx] = s;
+#pragma unroll
+  for (int k = 1; k < LR; k <<= 1) s += __shfl_xor(s, k, WAVE);
+  if (in && c == 0) {
+    const int h = r % a.Hq;
+    const int64_t row = r / a.Hq, b = row / a.S, i = row % a.S;
+    a.delta[(b * a.Hq + h) * a.S + i] = s;
+  }
 }
 
-// dq for query row i of head h
+// dq of 32 queries of head h
 template <typename T, int HD>
-__global__ void __launch_bounds__(TR) attn_bwd_dq(AttnArgs a) {
-  __shared__ float Ks[TR][HD];
-  __shared__ float Vs[TR][HD];
+__device__ __forceinline__ void bwd_dq(const AttnArgs& a, int qb, int h, int b, float* red) {
   const Geo g(a);
-  const int b = blockIdx.z, h = blockIdx.y, kvh = h / g.group;
-  const int i = blockIdx.x * TR + threadIdx.x;
-  const int ic = min(i, a.S - 1);
-  const T* qkv = (const T*)a.qkv;
-  const T* dO = (const T*)a.dout;
+  const int kvh = h / g.group, q0 = qb * TR;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, q = q0 + lane % 32, qc = min(q, a.S - 1);
+  const T* qkv = (const T*)a.qkv + (int64_t)b * a.S * g.ld;
+  const T* kp = qkv + g.koff + kvh * HD;
+  const T* vp = qkv + g.voff + kvh * HD;
   const float scale = 1.0f / sqrtf((float)HD);
-  float q[HD], dq[HD], d_o[HD];
-  const int64_t rowq = (int64_t)(b * a.S + ic) * g.ld;
-  const int64_t rowo = (int64_t)(b * a.S + ic) * a.Hq * HD + h * HD;
+  RowFrag<HD> qf, df;
+  qf.load(qkv + h * HD, qc, g.ld);
+  df.load((const T*)a.dout + (int64_t)b * a.S * a.Hq * HD + h * HD, qc, a.Hq * HD);
 #pragma unroll
-  for (int c = 0; c < HD; ++c) {
-    q[c] = to_f32(qkv[rowq + h * HD + c]) * scale;
-    d_o[c] = to_f32(dO[rowo + c]);
-    dq[c] = 0.f;
-  }
-  const int64_t sidx = ((int64_t)b * a.Hq + h) * a.S + ic;
+  for (int i = 0; i < HD / 8; ++i) qf.v[i] *= scale;
+  const int64_t sidx = ((int64_t)b * a.Hq + h) * a.S + qc;
   const float lse = a.lse[sidx], dl = a.delta[sidx];
-  const int last = min(a.S - 1, blockIdx.x * TR + TR - 1);
-  for (int j0 = 0; j0 <= last; j0 += TR) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < TR * HD; e += TR) {
-      const int r = e / HD, c = e % HD, j = j0 + r;
-      const int64_t row = (int64_t)(b * a.S + min(j, a.S - 1)) * g.ld;
-      Ks[r][c] = to_f32(qkv[row + g.koff + kvh * HD + c]);
-      Vs[r][c] = to_f32(qkv[row + g.voff + kvh * HD + c]);
-    }
-    __syncthreads();
-    const int jend = min(TR, i - j0 + 1);
-    for (int r = 0; r < jend; ++r) {
-      float s = 0.f, dp = 0.f;
+  f32x16 dq[HD / 32];
 #pragma unroll
-      for (int c = 0; c < HD; ++c) { s += q[c] * Ks[r][c]; dp += d_o[c] * Vs[r][c]; }
-      const float ds = expf(s - lse) * (dp - dl);
+  for (int dt = 0; dt < HD / 32; ++dt)
 #pragma unroll
-      for (int c = 0; c < HD; ++c) dq[c] += ds * Ks[r][c];
+    for (int e = 0; e < 16; ++e) dq[dt][e] = 0.f;
+  for (int k0 = wave * TR; k0 <= q0; k0 += NW * TR) {
+    const int kr = min(k0 + lane % 32, a.S - 1);
+    RowFrag<HD> f;
+    f.load(kp, kr, g.ld);
+    f32x16 s = rows_product<HD>(f, qf);
+    f.load(vp, kr, g.ld);
+    const f32x16 dp = rows_product<HD>(f, df);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const bool seen = k0 + 8 * (e / 4) + 4 * (lane / 32) + e % 4 <= q;
+      s[e] = seen ? expf(s[e] - lse) * (dp[e] - dl) : 0.f;
     }
+    cols_product<HD>(dq, kp, k0, a.S - 1, g.ld, s);
   }
-  if (i >= a.S) return;
-  T* dqkv = (T*)a.dqkv;
-#pragma unroll
-  for (int c = 0; c < HD; ++c) dqkv[rowq + h * HD + c] = from_f32<T>(dq[c] * scale);
+  put_partial<HD>(red, dq, 1.0f);
+  __syncthreads();
+  store_rows<HD>(red, scale, (T*)a.dqkv + (int64_t)b * a.S * g.ld + h * HD, g.ld, q0, a.S, a.rope_cos, a.rope_sin);
 }
 
-// dk (WANT_DK) or dv for key row j of key/value head kvh, summed over its query heads
-template <typename T, int HD, bool WANT_DK>
-__global__ void __launch_bounds__(TR) attn_bwd_dkv(AttnArgs a) {
-  __shared__ float Qs[TR][HD];
-  __shared__ float Ds[TR][HD];
-  __shared__ float Ls[TR], Dl[TR];
+// dk and dv of 32 keys of key/value head kvh, summed over its query heads
+template <typename T, int HD>
+__device__ __forceinline__ void bwd_dkv(const AttnArgs& a, int kb, int kvh, int b, float* red) {
   const Geo g(a);
-  const int b = blockIdx.z, kvh = blockIdx.y;
-  const int j = blockIdx.x * TR + threadIdx.x;
-  const int jc = min(j, a.S - 1);
-  const T* qkv = (const T*)a.qkv;
-  const T* dO = (const T*)a.dout;
+  const int k0 = kb * TR;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, key = k0 + lane % 32, kc = min(key, a.S - 1);
+  const T* qkv = (const T*)a.qkv + (int64_t)b * a.S * g.ld;
   const float scale = 1.0f / sqrtf((float)HD);
-  float k[HD], v[HD], acc[HD];
-  const int64_t rowk = (int64_t)(b * a.S + jc) * g.ld;
+  RowFrag<HD> kf, vf;
+  kf.load(qkv + g.koff + kvh * HD, kc, g.ld);
+  vf.load(qkv + g.voff + kvh * HD, kc, g.ld);
 #pragma unroll
-  for (int c = 0; c < HD; ++c) {
-    k[c] = to_f32(qkv[rowk + g.koff + kvh * HD + c]);
-    v[c] = WANT_DK ? to_f32(qkv[rowk + g.voff + kvh * HD + c]) : 0.f;
-    acc[c] = 0.f;
-  }
-  const int first = blockIdx.x * TR;
-  for (int hh = 0; hh < g.group; ++hh) {
-    const int h = kvh * g.group + hh;
-    for (int i0 = first; i0 < a.S; i0 += TR) {
-      __syncthreads();
-      for (int e = threadIdx.x; e < TR * HD; e += TR) {
-        const int r = e / HD, c = e % HD, i = min(i0 + r, a.S - 1);
-        Qs[r][c] = to_f32(qkv[(int64_t)(b * a.S + i) * g.ld + h * HD + c]) * scale;
-        Ds[r][c] = to_f32(dO[(int64_t)(b * a.S + i) * a.Hq * HD + h * HD + c]);
-      }
-      {
-        const int i = min(i0 + (int)threadIdx.x, a.S - 1);
-        const int64_t sidx = ((int64_t)b * a.Hq + h) * a.S + i;
-        Ls[threadIdx.x] = a.lse[sidx];
-        Dl[threadIdx.x] = WANT_DK ? a.delta[sidx] : 0.f;
-      }
-      __syncthreads();
-      const int rend = min(TR, a.S - i0);
-      for (int r = 0; r < rend; ++r) {
-        if (i0 + r < j) continue;  // causal: query i >= key j
-        float s = 0.f;
+  for (int i = 0; i < HD / 8; ++i) kf.v[i] *= scale;
+  f32x16 dk[HD / 32], dv[HD / 32];
 #pragma unroll
-        for (int c = 0; c < HD; ++c) s += Qs[r][c] * k[c];
-        const float p = expf(s - Ls[r]);
-        if (WANT_DK) {
-          float dp = 0.f;
+  for (int dt = 0; dt < HD / 32; ++dt)
 #pragma unroll
-          for (int c = 0; c < HD; ++c) dp += Ds[r][c] * v[c];
-          const float ds = p * (dp - Dl[r]);
+    for (int e = 0; e < 16; ++e) { dk[dt][e] = 0.f; dv[dt][e] = 0.f; }
+  // tiles: every query tile at or after the keys, of every query head of the group
+  const int nt = (a.S + TR - 1) / TR - kb;
+  for (int it = wave; it < g.group * nt; it += NW) {
+    const int h = kvh * g.group + it / nt, q0 = k0 + (it % nt) * TR;
+    const T* qp = qkv + h * HD;
+    const T* dp_ = (const T*)a.dout + (int64_t)b * a.S * a.Hq * HD + h * HD;
+    const int64_t sb = ((int64_t)b * a.Hq + h) * a.S;
+    const int qr = min(q0 + lane % 32, a.S - 1);
+    RowFrag<HD> f;
+    f.load(qp, qr, g.ld);
+    f32x16 p = rows_product<HD>(f, kf);  // rows: queries; column: this lane's key
+    f.load(dp_, qr, a.Hq * HD);
+    f32x16 ds = rows_product<HD>(f, vf);
 #pragma unroll
-          for (int c = 0; c < HD; ++c) acc[c] += ds * Qs[r][c];  // Qs already holds q * scale
-        } else {
-#pragma unroll
-          for (int c = 0; c < HD; ++c) acc[c] += p * Ds[r][c];
-        }
-      }
+    for (int e = 0; e < 16; ++e) {
+      const int q = q0 + 8 * (e / 4) + 4 * (lane / 32) + e % 4, qc = min(q, a.S - 1);
+      p[e] = q >= key && q < a.S ? expf(p[e] - a.lse[sb + qc]) : 0.f;
+      ds[e] = p[e] * (ds[e] - a.delta[sb + qc]);
     }
+    cols_product<HD>(dv, dp_, q0, a.S - 1, a.Hq * HD, p);
+    cols_product<HD>(dk, qp, q0, a.S - 1, g.ld, ds);
   }
-  if (j >= a.S) return;
-  T* dqkv = (T*)a.dqkv;
-  const int off = WANT_DK ? g.koff : g.voff;
-#pragma unroll
-  for (int c = 0; c < HD; ++c) dqkv[rowk + off + kvh * HD + c] = from_f32<T>(acc[c]);
+  T* out = (T*)a.dqkv + (int64_t)b * a.S * g.ld;
+  put_partial<HD>(red, dk, 1.0f);
+  __syncthreads();
+  store_rows<HD>(red, scale, out + g.koff + kvh * HD, g.ld, k0, a.S, a.rope_cos, a.rope_sin);
+  __syncthreads();
+  put_partial<HD>(red, dv, 1.0f);
+  __syncthreads();
+  store_rows<HD>(red, 1.0f, out + g.voff + kvh * HD, g.ld, k0, a.S, nullptr, nullptr);
+}
+
+// dk/dv blocks (first, low keys see the most queries) and dq blocks (longest ranges first) in one
+// launch: independent given delta, and together they fill more of the chip.
+template <typename T, int HD>
+__global__ void __launch_bounds__(NW * 64) attn_bwd(AttnArgs a) {
+  __shared__ float red[NW * (HD / 32) * 16 * 64];
+  const int h = blockIdx.y, b = blockIdx.z;
+  if (h < a.Hkv) bwd_dkv<T, HD>(a, blockIdx.x, h, b, red);
+  else bwd_dq<T, HD>(a, gridDim.x - 1 - blockIdx.x, h - a.Hkv, b, red);
 }
 
 template <typename T, int HD>
 void fwd_t(const AttnArgs& a, hipStream_t st) {
-  attn_fwd<T, HD><<<dim3((unsigned)cdiv(a.S, TR), a.Hq, a.B), TR, 0, st>>>(a);
+  attn_fwd<T, HD><<<dim3((unsigned)cdiv(a.S, TR), a.Hq, a.B), NW * 64, 0, st>>>(a);
 }
 template <typename T, int HD>
 void delta_t(const AttnArgs& a, hipStream_t st) {
-  attn_delta<T, HD><<<(unsigned)cdiv((int64_t)a.B * a.Hq * a.S, 256), 256, 0, st>>>(a);
+  attn_delta<T, HD><<<(unsigned)cdiv((int64_t)a.B * a.Hq * a.S * (HD / 4), 256), 256, 0, st>>>(a);
 }
 template <typename T, int HD>
 void bwd_t(const AttnArgs& a, hipStream_t st) {
   if (!a.delta_ready) delta_t<T, HD>(a, st);
-  attn_bwd_dq<T, HD><<<dim3((unsigned)cdiv(a.S, TR), a.Hq, a.B), TR, 0, st>>>(a);
-  attn_bwd_dkv<T, HD, false><<<dim3((unsigned)cdiv(a.S, TR), a.Hkv, a.B), TR, 0, st>>>(a);
-  attn_bwd_dkv<T, HD, true><<<dim3((unsigned)cdiv(a.S, TR), a.Hkv, a.B), TR, 0, st>>>(a);
+  attn_bwd<T, HD><<<dim3((unsigned)cdiv(a.S, TR), a.Hkv + a.Hq, a.B), NW * 64, 0, st>>>(a);
 }
 
-template <typename T>
-void fwd_hd(const AttnArgs& a, hipStream_t st) {
-  if (a.hd == 32) fwd_t<T, 32>(a, st);
-  else if (a.hd == 64) fwd_t<T, 64>(a, st);
-  else fwd_t<T, 128>(a, st);
+template <typename T, typename F>
+void dispatch_hd(int hd, F&& run) {
+  if (hd == 32) run(T{}, std::integral_constant<int, 32>{});
+  else if (hd == 64) run(T{}, std::integral_constant<int, 64>{});
+  else run(T{}, std::integral_constant<int, 128>{});
 }
-template <typename T>
-void bwd_hd(const AttnArgs& a, hipStream_t st) {
-  if (a.hd == 32) bwd_t<T, 32>(a, st);
-  else if (a.hd == 64) bwd_t<T, 64>(a, st);
-  else bwd_t<T, 128>(a, st);
+template <typename F>
+void dispatch(bool bf, int hd, F&& run) {  // run(type tag, head dimension)
+  if (bf) dispatch_hd<bf16>(hd, run);
+  else dispatch_hd<float>(hd, run);
 }
 
 }  // namespace
 
-void launch_attention_fwd_ref(bool bf, const AttnArgs& a, hipStream_t st) {
-  if (bf) fwd_hd<bf16>(a, st); else fwd_hd<float>(a, st);
-}
-void launch_attention_bwd_ref(bool bf, const AttnArgs& a, hipStream_t st) {
-  if (bf) bwd_hd<bf16>(a, st); else bwd_hd<float>(a, st);
-}
-
 void launch_attention_fwd(bool bf, const AttnArgs& a, hipStream_t st) {
   if (bf && attention_mfma_fwd_try(a, st)) return;
-  launch_attention_fwd_ref(bf, a, st);
+  dispatch(bf, a.hd, [&](auto t, auto hd) { fwd_t<decltype(t), decltype(hd)::value>(a, st); });
 }
 void launch_attention_delta(bool bf, const AttnArgs& a, hipStream_t st) {
   if (bf && attention_mfma_delta_try(a, st)) return;
-  auto run = [&](auto tag) {
-    using T = decltype(tag);
-    if (a.hd == 32) delta_t<T, 32>(a, st);
-    else if (a.hd == 64) delta_t<T, 64>(a, st);
-    else delta_t<T, 128>(a, st);
-  };
-  if (bf) run(bf16{}); else run(float{});
+  dispatch(bf, a.hd, [&](auto t, auto hd) { delta_t<decltype(t), decltype(hd)::value>(a, st); });
 }
-
 void launch_attention_bwd(bool bf, const AttnArgs& a, hipStream_t st) {
   if (bf && attention_mfma_bwd_try(a, st)) return;
-  launch_attention_bwd_ref(bf, a, st);
-  if (a.rope_cos)  // dq, dk back through the rotation (query heads and key heads are contiguous)
-    launch_rope(bf, a.dqkv, a.B * a.S, a.S, a.Hq + a.Hkv, a.hd, (a.Hq + 2 * a.Hkv) * a.hd, a.rope_cos,
-                a.rope_sin, true, st);
+  dispatch(bf, a.hd, [&](auto t, auto hd) { bwd_t<decltype(t), decltype(hd)::value>(a, st); });
 }
