@@ -185,11 +185,7 @@ __device__ __forceinline__ void ring_wait(bool more) {
 // With rope tables the rows are gradients w.r.t. RoPE-rotated vectors and leave rotated back by
 // -angle(position, i) (position = row within the sequence): the gradient w.r.t. the unrotated ones.
 template <int HD>
-__device__ __forceinline__ void store_rows_from_t(float* __restrict__ stage, const f32x16* acc, float scale,
-                                                  bf16* __restrict__ out, int ldo, int row0_wg, int S,
-                                                  const float* rope_cos = nullptr,
-                                                  const float* rope_sin = nullptr,
-                                                  float* __restrict__ out32 = nullptr) {
+__device__ __forceinline__ void stage_rows_from_t(float* __restrict__ stage, const f32x16* acc, float scale) {
   constexpr int OP = HD + 4;  // fp32 staging pitch
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, half = lane / 32, col = lane % 32;
 #pragma unroll
@@ -198,6 +194,15 @@ __device__ __forceinline__ void store_rows_from_t(float* __restrict__ stage, con
     for (int e = 0; e < 16; ++e)
       stage[(wave * 32 + col) * OP + dt * 32 + 8 * (e / 4) + 4 * half + (e % 4)] = acc[dt][e] * scale;
   __syncthreads();
+}
+template <int HD>
+__device__ __forceinline__ void store_rows_from_t(float* __restrict__ stage, const f32x16* acc, float scale,
+                                                  bf16* __restrict__ out, int ldo, int row0_wg, int S,
+                                                  const float* rope_cos = nullptr,
+                                                  const float* rope_sin = nullptr,
+                                                  float* __restrict__ out32 = nullptr) {
+  constexpr int OP = HD + 4;
+  stage_rows_from_t<HD>(stage, acc, scale);
   for (int c = threadIdx.x; c < QB * HD / 8; c += NT) {
     const int r = c / (HD / 8), d = (c % (HD / 8)) * 8;
     const int row = row0_wg + r;
@@ -224,6 +229,19 @@ __device__ __forceinline__ void store_rows_from_t(float* __restrict__ stage, con
       }
     }
     *reinterpret_cast<bf16x8*>(out + (int64_t)row * ldo + d) = ov;
+  }
+  __syncthreads();
+}
+
+// The same rows in fp32, unscaled (partial sums of a split dK/dV item)
+template <int HD>
+__device__ __forceinline__ void store_partial_from_t(float* __restrict__ stage, const f32x16* acc,
+                                                     float* __restrict__ out, int ldo, int row0_wg, int S) {
+  stage_rows_from_t<HD>(stage, acc, 1.0f);
+  for (int c = threadIdx.x; c < QB * HD / 4; c += NT) {
+    const int r = c / (HD / 4), d = (c % (HD / 4)) * 4, row = row0_wg + r;
+    if (row < S)
+      *reinterpret_cast<f32x4*>(out + (int64_t)row * ldo + d) = *reinterpret_cast<const f32x4*>(stage + r * (HD + 4) + d);
   }
   __syncthreads();
 }
@@ -576,7 +594,7 @@ __global__ void __launch_bounds__(NT) flash_bwd_dq(AttnArgs a) {
 
 // ------------------------------------------------------------------------------------------ dK, dV
 template <int HD>
-__device__ __forceinline__ void bwd_dkv_block(const AttnArgs& a, int bx, int by, int bz,
+__device__ __forceinline__ void bwd_dkv_block(const AttnArgs& a, int bx, int split, int by, int bz,
     unsigned char* __restrict__ smem) {
   using L = Lds<HD>;
   using TT = DmaRowTile<HD>;
@@ -596,7 +614,9 @@ __device__ __forceinline__ void bwd_dkv_block(const AttnArgs& a, int bx, int by,
   const int qblk0 = (kbk * QB) / KB;
   const int nqblk = (a.S + KB - 1) / KB;
   const int per_head = nqblk - qblk0;
-  const int nit = group * per_head;
+  // of which this item takes its share [it0, nit) of nsplit
+  const int it0 = (int)((int64_t)group * per_head * split / a.nsplit);
+  const int nit = (int)((int64_t)group * per_head * (split + 1) / a.nsplit);
   // each wave loads one row vector per stage: waves 0 and 2 the lse values, 1 and 3 the deltas
   // (the same data twice, so that every thread has the same number of loads in flight)
   const float* rowv = (__builtin_amdgcn_readfirstlane(wave) & 1) ? a.delta : a.lse;
@@ -622,14 +642,14 @@ __device__ __forceinline__ void bwd_dkv_block(const AttnArgs& a, int bx, int by,
   wait_vm_lds<0>();  // register loads done before the ring starts (as in the forward)
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
-    if (s < nit) issue(s);
+    if (it0 + s < nit) issue(it0 + s);
   const float sl2 = LOG2E / sqrtf((float)HD);
   f32x16 dk[DT], dv[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) { dk[dt][e] = 0.f; dv[dt][e] = 0.f; }
-  for (int it = 0; it < nit; ++it) {
+  for (int it = it0; it < nit; ++it) {
     ring_wait<NS, 2 * TT::PER + 1>(it + 1 < nit);
     block_barrier();  // every thread's loads of iteration it are in; every wave is done with it - 1
     if (it + NS - 1 < nit) issue(it + NS - 1);
@@ -773,6 +793,13 @@ __device__ __forceinline__ void bwd_dkv_block(const AttnArgs& a, int bx, int by,
     }
   }
   block_barrier();  // every wave is done with the last stage: the ring becomes the output staging
+  if (a.nsplit > 1) {
+    const int kvd = a.Hkv * HD;
+    float* p = a.part + ((int64_t)split * 2 * a.B + b) * a.S * kvd + kvh * HD;
+    store_partial_from_t<HD>(reinterpret_cast<float*>(smem), dk, p, kvd, kbk * QB, a.S);
+    store_partial_from_t<HD>(reinterpret_cast<float*>(smem), dv, p + (int64_t)a.B * a.S * kvd, kvd, kbk * QB, a.S);
+    return;
+  }
   bf16* outb = (bf16*)a.dqkv + (int64_t)b * a.S * ld;
   store_rows_from_t<HD>(reinterpret_cast<float*>(smem), dk, 1.0f / sqrtf((float)HD), outb + (a.Hq + kvh) * HD, ld,
                         kbk * QB, a.S, a.rope_cos, a.rope_sin);
@@ -785,26 +812,70 @@ __global__ void __launch_bounds__(NT) flash_bwd_dkv(AttnArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int nkb = (a.S + QB - 1) / QB;
   int unit, idx;  // unit: (batch, key/value head); low key blocks (the most queries) first
-  xcd_item(blockIdx.x, nkb * a.Hkv * a.B, nkb, unit, idx);
-  bwd_dkv_block<HD>(a, idx, unit % a.Hkv, unit / a.Hkv, smem);
+  xcd_item(blockIdx.x, nkb * a.nsplit * a.Hkv * a.B, nkb * a.nsplit, unit, idx);
+  bwd_dkv_block<HD>(a, idx / a.nsplit, idx % a.nsplit, unit % a.Hkv, unit / a.Hkv, smem);
 }
 
 // dQ and dK/dV work items in one launch (independent given delta), so the two fill the CUs
 // together instead of each leaving a tail.  A unit is one (batch, key/value head): its dK/dV items
 // and the dQ items of its query heads, which all stream that head group's rows, on one XCD.
-// Within a unit, level k holds dK/dV block k and query block nb - 1 - k of each query head: the
-// items of one level have the same causal extent, and heavier levels come first.
+// Within a unit, level k holds dK/dV block k (its nsplit shares) and query block nb - 1 - k of each
+// query head: the items of one level have the same causal extent, and heavier levels come first.
 template <int HD>
 __global__ void __launch_bounds__(NT) flash_bwd_fused(AttnArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int nb = (a.S + QB - 1) / QB;
-  const int group = a.Hq / a.Hkv, per_unit = nb * (group + 1);
+  const int group = a.Hq / a.Hkv, per_level = group + a.nsplit, per_unit = nb * per_level;
   int unit, idx;
   xcd_item(blockIdx.x, per_unit * a.Hkv * a.B, per_unit, unit, idx);
   const int kvh = unit % a.Hkv, b = unit / a.Hkv;
-  const int level = idx / (group + 1), j = idx % (group + 1);
-  if (j == 0) bwd_dkv_block<HD>(a, level, kvh, b, smem);
-  else bwd_dq_block<HD>(a, level, kvh * group + j - 1, b, smem);
+  const int level = idx / per_level, j = idx % per_level;
+  if (j < a.nsplit) bwd_dkv_block<HD>(a, level, j, kvh, b, smem);
+  else bwd_dq_block<HD>(a, level, kvh * group + j - a.nsplit, b, smem);
+}
+
+// dk and dv of a split backward: the nsplit partial sums added in order, 8 columns per thread, dk
+// scaled and rotated back
+template <int HD>
+__global__ void __launch_bounds__(256) dkv_reduce(AttnArgs a) {
+  constexpr int HH = HD / 2;
+  const int kvd = a.Hkv * HD, ld = (a.Hq + 2 * a.Hkv) * HD;
+  const int64_t rows = (int64_t)a.B * a.S, n = rows * kvd;
+  const int64_t c = 8 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
+  if (c >= 2 * n) return;
+  const bool isv = c >= n;
+  const int64_t e = isv ? c - n : c;
+  const int64_t row = e / kvd;
+  const int col = (int)(e % kvd), d = col % HD;
+  auto sum = [&](int64_t o, f32x4& lo, f32x4& hi) {  // elements o .. o + 7 of the first partial
+    lo = *reinterpret_cast<const f32x4*>(a.part + o);
+    hi = *reinterpret_cast<const f32x4*>(a.part + o + 4);
+    for (int s = 1; s < a.nsplit; ++s) {
+      lo += *reinterpret_cast<const f32x4*>(a.part + 2 * n * s + o);
+      hi += *reinterpret_cast<const f32x4*>(a.part + 2 * n * s + o + 4);
+    }
+  };
+  f32x4 v[2], p[2];
+  sum(c, v[0], v[1]);
+  if (!isv) {
+    const float scale = 1.0f / sqrtf((float)HD);
+    const bool first = d < HH;
+    if (a.rope_cos) sum(first ? c + HH : c - HH, p[0], p[1]);
+    const int64_t t = (row % a.S) * HH + d % HH;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      float x = v[q / 4][q % 4] * scale;
+      if (a.rope_cos) {
+        const float y = p[q / 4][q % 4] * scale, cs = a.rope_cos[t + q], sn = a.rope_sin[t + q];
+        x = first ? x * cs + y * sn : x * cs - y * sn;
+      }
+      v[q / 4][q % 4] = x;
+    }
+  }
+  bf16x8 ov;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) ov[q] = (bf16)v[q / 4][q % 4];
+  *reinterpret_cast<bf16x8*>((bf16*)a.dqkv + row * ld + (a.Hq + (isv ? a.Hkv : 0)) * HD + col) = ov;
 }
 
 // delta[b, h, i] = sum_d dO[b, i, h, d] O[b, i, h, d]; one thread per (token, head)
@@ -852,7 +923,9 @@ void fwd_launch(const AttnArgs& a, hipStream_t st) {
 }
 
 template <int HD>
-void bwd_launch(const AttnArgs& a, hipStream_t st) {
+void bwd_launch(const AttnArgs& args, hipStream_t st) {
+  AttnArgs a = args;
+  a.nsplit = a.part ? attention_dkv_splits(a.B, a.S, a.Hq, a.Hkv, HD) : 1;
   static bool attr = false;
   if (!attr) {
     set_lds(flash_bwd_dq<HD>, Lds<HD>::dq_bytes());
@@ -868,14 +941,24 @@ void bwd_launch(const AttnArgs& a, hipStream_t st) {
     const size_t bytes = std::max(Lds<HD>::dq_bytes(), Lds<HD>::dkv_bytes());
     if (!fattr) { set_lds(flash_bwd_fused<HD>, bytes); fattr = true; }
     const int nb = (int)cdiv(a.S, QB);
-    flash_bwd_fused<HD><<<(unsigned)(nb * (a.Hq + a.Hkv) * a.B), NT, bytes, st>>>(a);
+    flash_bwd_fused<HD><<<(unsigned)(nb * (a.Hq + a.nsplit * a.Hkv) * a.B), NT, bytes, st>>>(a);
   } else {
     flash_bwd_dq<HD><<<(unsigned)(cdiv(a.S, QB) * a.Hq * a.B), NT, Lds<HD>::dq_bytes(), st>>>(a);
-    flash_bwd_dkv<HD><<<(unsigned)(cdiv(a.S, QB) * a.Hkv * a.B), NT, Lds<HD>::dkv_bytes(), st>>>(a);
+    flash_bwd_dkv<HD><<<(unsigned)(cdiv(a.S, QB) * a.nsplit * a.Hkv * a.B), NT, Lds<HD>::dkv_bytes(), st>>>(a);
   }
+  if (a.nsplit > 1)
+    dkv_reduce<HD><<<(unsigned)cdiv(2 * (int64_t)a.B * a.S * a.Hkv * HD / 8, 256), 256, 0, st>>>(a);
 }
 
 }  // namespace
+
+// A dK/dV item walks group x S / 64 tiles of queries, so a few key/value heads leave the chip to the
+// longest items: below 512 items (two per CU) each is split, keeping at least 8 tiles to the longest.
+int attention_dkv_splits(int B, int S, int Hq, int Hkv, int hd) {
+  if (hd != 64 && hd != 128) return 1;
+  const int64_t items = cdiv(S, QB) * Hkv * B, tiles = (int64_t)(Hq / Hkv) * cdiv(S, KB);
+  return (int)std::max<int64_t>(1, std::min<int64_t>({8, cdiv(512, items), tiles / 8}));
+}
 
 bool attention_mfma_fwd_try(const AttnArgs& a, hipStream_t st) {
   if ((uintptr_t)a.qkv % 16 || (uintptr_t)a.o % 16 || (uintptr_t)a.o32 % 16) return false;

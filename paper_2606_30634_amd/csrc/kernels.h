@@ -167,7 +167,17 @@ struct AttnArgs {
   float* o32 = nullptr;
   const float* rope_cos = nullptr; const float* rope_sin = nullptr;
   bool delta_ready = false;  // backward: delta already holds rowsum(dO O)
+  // backward, head dims 64 and 128 in bf16: fp32 workspace of attention_part_elems(), when not null,
+  // for the partial dk, dv of split items ([split][dk, dv][B S][Hkv hd]); nsplit is the launcher's
+  float* part = nullptr;
+  int nsplit = 1;
 };
+// how many items share a dk/dv row block in the bf16 backward of this shape
+int attention_dkv_splits(int B, int S, int Hq, int Hkv, int hd);
+inline int64_t attention_part_elems(int B, int S, int Hq, int Hkv, int hd) {
+  const int ns = attention_dkv_splits(B, S, Hq, Hkv, hd);
+  return ns > 1 ? 2 * (int64_t)ns * B * S * Hkv * hd : 0;
+}
 void launch_attention_fwd(bool bf, const AttnArgs& a, hipStream_t st);
 // delta = rowsum(dO O) per (batch, head, query) alone (O from o32 when set)
 void launch_attention_delta(bool bf, const AttnArgs& a, hipStream_t st);

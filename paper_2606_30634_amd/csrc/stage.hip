@@ -139,6 +139,7 @@ struct stage {
   float *delta, *rms_part, *row_loss, *cos_t, *sin_t, *norm_out, *upd_norm_out;
   double *norm_part, *upd_norm_part;
   float* gemm_ws;
+  float* attn_part;  // partial dk, dv of the attention backward's split items (null: none are split)
   int* flag;
   unsigned long long* skipped;
   int32_t* sort_ws;  // the token sort's scratch (its sorts run in order on one stream)
@@ -398,6 +399,9 @@ size_t layout(stage* S, char* base) {
   S->upd_norm_part = (double*)carve(norm_scratch_bytes());
   S->upd_norm_out = (float*)carve(2 * 4);
   S->gemm_ws = sh.dtype == 1 ? (float*)carve(GEMM_WS_ELEMS * 4) : nullptr;
+  const int64_t part = sh.dtype == 1
+      ? attention_part_elems(sh.micro_batch, sh.seq_len, sh.n_heads, sh.n_kv_heads, sh.head_dim) : 0;
+  S->attn_part = part ? (float*)carve(part * 4) : nullptr;
   S->norm_out = (float*)carve(2 * 4);
   S->flag = (int*)carve(4);
   S->skipped = (unsigned long long*)carve(8);
@@ -645,7 +649,7 @@ void block_backward(stage* S, int vi, BlockAct& b, const BlockOff& w, const void
   run_gemm(S, go);
   run_wgrad(S, gemm(d, S->hqd, T, S->dh, d, false, b.o, S->hqd, false, g + w.wo, S->hqd, true, beta), WG_O);
   AttnArgs a = attn_args(S, b);
-  a.dout = S->do_; a.dqkv = S->dqkv; a.delta = S->delta;
+  a.dout = S->do_; a.dqkv = S->dqkv; a.delta = S->delta; a.part = S->attn_part;
   a.delta_ready = true;  // computed with do above
   a.rope_cos = S->cos_t;  // dq, dk come back w.r.t. the unrotated projections
   a.rope_sin = S->sin_t;
