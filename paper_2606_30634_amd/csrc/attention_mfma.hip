@@ -162,6 +162,11 @@ struct DmaRowTile {
 #pragma unroll
     for (int q = 0; q < PER; ++q) dma16(t, voff(q, ld, S - row0), lds + w + (uint32_t)q * (NT / 64) * 1024u);
   }
+  // This thread's q-th load with a range that ends with the head's last row (rows past it arrive as
+  // zeros); lds: the tile's address plus 1 KB per wave.
+  __device__ static void issue_range(u32x4 range, int q, int ld, uint32_t lds) {
+    dma16_range(range, voff(q, ld, KB), lds + (uint32_t)q * (NT / 64) * 1024u);
+  }
 };
 
 // stages of the streamed-tile ring: a tile's loads are issued NS - 1 iterations before it is used
@@ -658,136 +663,54 @@ __device__ __forceinline__ void bwd_dkv_block(const AttnArgs& a, int bx, int spl
     const float* Ls = reinterpret_cast<const float*>(Qs + 2 * L::TSZ);
     const float* Dl = Ls + KB;
     const int qs0 = (qblk0 + it % per_head) * KB;
-    if constexpr (HD == 128) {
-      // Both 32-query sub-tiles at once (one wave per SIMD at this head dim, so the wave's own
-      // instruction-level parallelism is what hides latency): the S and dP products of the two
-      // sub-tiles interleaved (four independent accumulator chains), then the softmax of each
-      // sub-tile beside the other's MFMAs.  A sub-tile whose queries all precede the wave's keys
-      // gets P = 0 from the causal mask, so it needs no branch.
-      f32x16 s2[2], dp2[2];
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < 2; ++t) {
+      const int q0t = qs0 + t * 32;
+      if (q0t + 31 < k0) continue;  // every query of this sub-tile precedes every key of the wave
+      f32x16 s, dp;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) { s2[t][e] = 0.f; dp2[t][e] = 0.f; }
-      // the Q and dO fragments of the next 16-deep step are read while this step's MFMAs run
-      bf16x8 fq[2][2], fd[2][2];
+      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        fq[0][t] = frag_rows<HD>(Qs, t * 32, 0);
-        fd[0][t] = frag_rows<HD>(Ds, t * 32, 0);
+      for (int ks = 0; ks < KS; ++ks) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HD>(Qs, t * 32, ks * 16), kf[ks], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HD>(Ds, t * 32, ks * 16), vf[ks], dp, 0, 0, 0);
       }
-      static_for<KS>([&](auto KSI) {
-        constexpr int ks = KSI, c = ks & 1;
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (ks + 1 < KS) {
+      // accumulator rows of this lane: t*32 + 8 (e/4) + 4 half + (e mod 4): four runs of 4
+      // consecutive query rows, so lse and delta arrive as 16-byte reads
+      // every query of the sub-tile sees every key of the wave and exists: no mask (head dim 64
+      // only, as in the dQ kernel)
+      const bool full = HD == 64 && q0t >= k0 + 31 && q0t + 31 < a.S;
 #pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            fq[c ^ 1][t] = frag_rows<HD>(Qs, t * 32, (ks + 1) * 16);
-            fd[c ^ 1][t] = frag_rows<HD>(Ds, t * 32, (ks + 1) * 16);
+      for (int e4 = 0; e4 < 4; ++e4) {
+        const int r0 = t * 32 + 8 * e4 + 4 * half;
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(Ls + r0);
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(Dl + r0);
+        if (full) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int e = 4 * e4 + j;
+            const float p = fast_exp2(__builtin_fmaf(s[e], sl2, -l4[j] * LOG2E));
+            s[e] = p;
+            dp[e] = p * (dp[e] - d4[j]);
           }
-        }
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          s2[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[c][t], kf[ks], s2[t], 0, 0, 0);
-          dp2[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fd[c][t], vf[ks], dp2[t], 0, 0, 0);
-        }
-        if constexpr (ks + 1 < KS) {
-          static_for<4>([&](auto) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
-          });
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      });
-      // dV and dK of each sub-tile: 16 MFMAs, (g2, dt, dV or dK), whose dO or Q fragments (two
-      // transposing reads each) stream through a ring of 4 read 3 MFMAs ahead; the first three
-      // go out before the sub-tile's softmax
-      constexpr int NC = 2 * DT * 2, RA = 3;
-      auto cfrag = [&](auto QI, int t) {
-        constexpr int q = QI, g2 = q / (2 * DT), dt = (q / 2) % DT, isk = q % 2;
-        return frag_cols<HD>(isk ? Qs : Ds, dt * 32, t * 32 + g2 * 16);
-      };
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        bf16x8 fc[RA + 1];
-        static_for<RA>([&](auto QI) { fc[(int)QI] = cfrag(QI, t); });
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          const int r0 = t * 32 + 8 * e4 + 4 * half;
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(Ls + r0);
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(Dl + r0);
+        } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             const int e = 4 * e4 + j, q = qs0 + r0 + j;
-            const float p = (q >= mykey && q < a.S) ? fast_exp2(__builtin_fmaf(s2[t][e], sl2, -l4[j] * LOG2E)) : 0.f;
-            s2[t][e] = p;
-            dp2[t][e] = p * (dp2[t][e] - d4[j]);
+            const float p = (q >= mykey && q < a.S) ? fast_exp2(__builtin_fmaf(s[e], sl2, -l4[j] * LOG2E)) : 0.f;
+            s[e] = p;
+            dp[e] = p * (dp[e] - d4[j]);
           }
         }
-        const bf16x8 pb0 = acc_rows_to_b<0>(s2[t]), pb1 = acc_rows_to_b<8>(s2[t]);
-        const bf16x8 sb0 = acc_rows_to_b<0>(dp2[t]), sb1 = acc_rows_to_b<8>(dp2[t]);
-        static_for<NC>([&](auto QI) {
-          constexpr int q = QI, g2 = q / (2 * DT), dt = (q / 2) % DT, isk = q % 2;
-          __builtin_amdgcn_sched_barrier(0);
-          if constexpr (q + RA < NC) fc[(q + RA) % (RA + 1)] = cfrag(std::integral_constant<int, q + RA>{}, t);
-          if constexpr (isk)
-            dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[q % (RA + 1)], g2 ? sb1 : sb0, dk[dt], 0, 0, 0);
-          else
-            dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[q % (RA + 1)], g2 ? pb1 : pb0, dv[dt], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-        });
       }
-    } else {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int q0t = qs0 + t * 32;
-        if (q0t + 31 < k0) continue;  // every query of this sub-tile precedes every key of the wave
-        f32x16 s, dp;
+      for (int g2 = 0; g2 < 2; ++g2) {
+        const bf16x8 pb = g2 ? acc_rows_to_b<8>(s) : acc_rows_to_b<0>(s);
+        const bf16x8 sb = g2 ? acc_rows_to_b<8>(dp) : acc_rows_to_b<0>(dp);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HD>(Qs, t * 32, ks * 16), kf[ks], s, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HD>(Ds, t * 32, ks * 16), vf[ks], dp, 0, 0, 0);
-        }
-        // accumulator rows of this lane: t*32 + 8 (e/4) + 4 half + (e mod 4): four runs of 4
-        // consecutive query rows, so lse and delta arrive as 16-byte reads
-        // every query of the sub-tile sees every key of the wave and exists: no mask (head dim 64
-        // only, as in the dQ kernel)
-        const bool full = HD == 64 && q0t >= k0 + 31 && q0t + 31 < a.S;
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          const int r0 = t * 32 + 8 * e4 + 4 * half;
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(Ls + r0);
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(Dl + r0);
-          if (full) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int e = 4 * e4 + j;
-              const float p = fast_exp2(__builtin_fmaf(s[e], sl2, -l4[j] * LOG2E));
-              s[e] = p;
-              dp[e] = p * (dp[e] - d4[j]);
-            }
-          } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int e = 4 * e4 + j, q = qs0 + r0 + j;
-              const float p = (q >= mykey && q < a.S) ? fast_exp2(__builtin_fmaf(s[e], sl2, -l4[j] * LOG2E)) : 0.f;
-              s[e] = p;
-              dp[e] = p * (dp[e] - d4[j]);
-            }
-          }
-        }
-#pragma unroll
-        for (int g2 = 0; g2 < 2; ++g2) {
-          const bf16x8 pb = g2 ? acc_rows_to_b<8>(s) : acc_rows_to_b<0>(s);
-          const bf16x8 sb = g2 ? acc_rows_to_b<8>(dp) : acc_rows_to_b<0>(dp);
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) {
-            dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols<HD>(Ds, dt * 32, t * 32 + g2 * 16), pb, dv[dt], 0, 0, 0);
-            dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols<HD>(Qs, dt * 32, t * 32 + g2 * 16), sb, dk[dt], 0, 0, 0);
-          }
+        for (int dt = 0; dt < DT; ++dt) {
+          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols<HD>(Ds, dt * 32, t * 32 + g2 * 16), pb, dv[dt], 0, 0, 0);
+          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols<HD>(Qs, dt * 32, t * 32 + g2 * 16), sb, dk[dt], 0, 0, 0);
         }
       }
     }
@@ -807,13 +730,265 @@ __device__ __forceinline__ void bwd_dkv_block(const AttnArgs& a, int bx, int spl
                         a.S);
 }
 
-template <int HD>
-__global__ void __launch_bounds__(NT) flash_bwd_dkv(AttnArgs a) {
+// dK/dV of head dimension 128.  The accumulators, K and V take 192 registers, so there is one wave per
+// SIMD, and a wave alone issues one instruction per ~5 cycles (2.1 ns measured, whatever its kind; an
+// MFMA runs 15 ns): what bounds the loop is its instruction count, about 950 per 64 MFMAs, and every
+// stall adds to it.  So the loop is pipelined over 32-query tiles n, each step holding the S and dP
+// products of tile n + 1, the softmax of tile n and the dV and dK products of tile n - 1, in 8 groups of
+// 4 MFMAs, each with the vector work of 2 accumulator elements per lane spread behind them, the LDS
+// reads of the next group (an LDS read lands within a group; 256 bytes per cycle, a fifth used) and one
+// load of the stage after.  Tiles n - 1 and n + 1 can lie in different stages, so the ring has three: an
+// iteration takes the score tiles of the newest stage and the products of the one before while the next
+// arrives.  Two sequences of 4096, 32 heads on 8: 697 -> 575 us (all products of a stage, then its
+// softmax, then the products before).
+//
+// acc += A B with the accumulator kept in accumulator registers (this file's builtin MFMAs keep theirs
+// in vector registers, which 128 more would overflow).  The compiler does not know the instruction, so
+// its distances are kept here: in the loop operands come from LDS reads (waited for) or vector
+// instructions several MFMAs back, and one accumulator's products are 16 MFMAs apart; COPIED (outside
+// the loop, where the compiler moves accumulators between registers) waits between such a move and the
+// product; and acc_settled() stands between the last products and any other read.
+template <bool COPIED>
+__device__ __forceinline__ void mfma_acc(f32x16& acc, const bf16x8& a, const bf16x8& b) {
+  if constexpr (COPIED) asm volatile("s_nop 4\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void acc_settled(f32x16 (&x)[4], f32x16 (&y)[4]) {
+  asm volatile("s_nop 15\n\ts_nop 15"
+               : "+a"(x[0]), "+a"(x[1]), "+a"(x[2]), "+a"(x[3]), "+a"(y[0]), "+a"(y[1]), "+a"(y[2]), "+a"(y[3]));
+}
+// keeps the computation of two values ahead of this point of the schedule
+__device__ __forceinline__ void pin(float& x, float& y) { asm volatile("" : "+v"(x), "+v"(y)); }
+
+struct Dkv128 {
+  static constexpr int HD = 128, KS = 8, DT = 4, NS = 3;
+  static constexpr int TSZ = KB * HD, SSZ = 2 * TSZ + 4 * KB;  // bf16 elements: Q, dO, lse and delta rows
+  static constexpr size_t bytes = (size_t)NS * SSZ * 2;
+  static_assert(bytes >= (size_t)QB * (HD + 4) * 4, "the ring holds the output staging");
+};
+
+__device__ __forceinline__ void bwd_dkv128_block(const AttnArgs& a, int kbk, int split, int kvh, int b,
+                                                 unsigned char* __restrict__ smem) {
+  using D = Dkv128;
+  constexpr int HD = D::HD, KS = D::KS, DT = D::DT, NS = D::NS;
+  using TT = DmaRowTile<HD>;
+  bf16* ring = reinterpret_cast<bf16*>(smem);
+  const int group = a.Hq / a.Hkv;
+  const int ld = (a.Hq + 2 * a.Hkv) * HD, hqd = a.Hq * HD;
+  const bf16* base = (const bf16*)a.qkv + (int64_t)b * a.S * ld;
+  const bf16* dbase = (const bf16*)a.dout + (int64_t)b * a.S * hqd;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, half = lane / 32, col = lane % 32;
+  const int mykey = kbk * QB + wave * 32 + col;
+  // iterations: every (query head of the group, 64-query tile at or after this key block), of which
+  // this item takes its share [it0, nit) of nsplit
+  const int qblk0 = (kbk * QB) / KB;
+  const int per_head = (a.S + KB - 1) / KB - qblk0;
+  const int it0 = (int)((int64_t)group * per_head * split / a.nsplit);
+  const int nit = (int)((int64_t)group * per_head * (split + 1) / a.nsplit);
+  const int wu = __builtin_amdgcn_readfirstlane(wave);
+  // each wave loads one row vector per stage: waves 0 and 2 the lse values, 1 and 3 the deltas
+  const float* rowv = ((wu & 1) ? a.delta : a.lse) + (int64_t)b * a.Hq * a.S;
+  // The tile being loaded (head h, queries q0 .. of 64), its stage slot, and the ranges of its rows.
+  // Queries past the sequence: zero rows of Q and dO, lse and delta 0, so P = 1, dS = 0 and nothing is
+  // added.
+  struct Fetch {
+    int h, q0, slot;
+    u32x4 q, d, r;
+    uint32_t lds;
+  } f;
+  f.h = kvh * group + it0 / per_head;
+  f.q0 = (qblk0 + it0 % per_head) * KB;
+  f.slot = 0;
+  auto ranges = [&] {
+    const bf16 *qh = base + f.h * HD, *dh = dbase + f.h * HD;
+    const float* rh = rowv + (int64_t)f.h * a.S;
+    f.q = buffer_range(qh + (int64_t)f.q0 * ld, qh + (int64_t)(a.S - 1) * ld + HD);
+    f.d = buffer_range(dh + (int64_t)f.q0 * hqd, dh + (int64_t)(a.S - 1) * hqd + HD);
+    f.r = buffer_range(rh + f.q0, rh + a.S);
+    f.lds = lds_addr(ring + f.slot * D::SSZ) + (uint32_t)wu * 1024u;
+  };
+  auto next_tile = [&] {  // past the item's last tile it wraps: loaded again, into a stage nobody reads
+    f.q0 += KB;
+    if (f.q0 >= a.S) {
+      f.q0 = qblk0 * KB;
+      f.h = f.h + 1 < (kvh + 1) * group ? f.h + 1 : kvh * group;
+    }
+    f.slot = f.slot + 1 < NS ? f.slot + 1 : 0;
+    ranges();
+  };
+  // load k of the 2 PER + 1 of a stage
+  auto fetch = [&](auto K_) {
+    constexpr int k = K_;
+    if constexpr (k < TT::PER) TT::issue_range(f.q, k, ld, f.lds);
+    else if constexpr (k < 2 * TT::PER) TT::issue_range(f.d, k - TT::PER, hqd, f.lds + D::TSZ * 2);
+    else dma4_range(f.r, 4u * (uint32_t)lane,
+                    lds_addr(ring + f.slot * D::SSZ + 2 * D::TSZ) + (uint32_t)(wu & 1) * KB * 4u);
+  };
+  static_assert(2 * TT::PER + 1 <= 2 * KS, "a load per group of the two steps");
+  bf16x8 kf[KS], vf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    if (mykey < a.S) {
+      kf[ks] = *reinterpret_cast<const bf16x8*>(base + (int64_t)mykey * ld + (a.Hq + kvh) * HD + ks * 16 + 8 * half);
+      vf[ks] = *reinterpret_cast<const bf16x8*>(base + (int64_t)mykey * ld + (a.Hq + a.Hkv + kvh) * HD + ks * 16 + 8 * half);
+    } else {
+      for (int j = 0; j < 8; ++j) { kf[ks][j] = (bf16)0.f; vf[ks][j] = (bf16)0.f; }
+    }
+  }
+  wait_vm_lds<0>();  // register loads done before the ring starts (as in the forward)
+  const float sl2 = LOG2E / sqrtf((float)HD);
+  f32x16 dk[DT], dv[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) { dk[dt][e] = 0.f; dv[dt][e] = 0.f; }
+  f32x16 s[2], dp[2];       // S and dP of the two tiles of a stage; after the softmax P and dS
+  bf16x8 pb[2][2], sb[2][2];  // P and dS as operands, two 16-query halves each
+
+  // One step.  With FE the loads of a stage, one per group (all at once would stall the wave on the
+  // address path), the first 8 with T = 0, the rest with T = 1.  S and dP of tile T of the stage at `rows` (SC); softmax of the other tile, whose first
+  // query is sq0, with the lse and delta rows at `stats` (SM); dV and dK of tile T of the stage at
+  // `cols`, from pb[T], sb[T] (PV).
+  auto step = [&](auto T_, auto SC_, auto SM_, auto PV_, auto FE_, const bf16* rows, const bf16* stats, int sq0,
+                  const bf16* cols) {
+    constexpr int T = T_, U = T ^ 1;
+    constexpr bool SC = SC_, SM = SM_, PV = PV_, FE = FE_;
+    const int lo = mykey - sq0 - 4 * half;  // first accumulator row of this lane that sees its key
+    const bf16 *Qr = rows, *Dr = rows + D::TSZ, *Qc = cols, *Dc = cols + D::TSZ;
+    const float* Ls = reinterpret_cast<const float*>(stats + 2 * D::TSZ) + U * 32 + 4 * half;
+    const float* Dl = Ls + KB;
+    // product q of the tile: 16-query half q / 8, columns 32 (q / 2 mod 4), dV (even) or dK (odd)
+    auto cfrag = [&](auto QI) {
+      constexpr int q = QI;
+      return frag_cols<HD>(q % 2 ? Qc : Dc, ((q / 2) % DT) * 32, T * 32 + (q / 8) * 16);
+    };
+    bf16x8 fq[2], fd[2], fc[4];
+    f32x4 l4[2], d4[2];
+    if constexpr (SM) {
+      l4[0] = *reinterpret_cast<const f32x4*>(Ls);
+      d4[0] = *reinterpret_cast<const f32x4*>(Dl);
+    }
+    if constexpr (SC) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) { s[T][e] = 0.f; dp[T][e] = 0.f; }
+      fq[0] = frag_rows<HD>(Qr, T * 32, 0);
+      fd[0] = frag_rows<HD>(Dr, T * 32, 0);
+    }
+    if constexpr (PV) {
+      fc[0] = cfrag(std::integral_constant<int, 0>{});
+      fc[1] = cfrag(std::integral_constant<int, 1>{});
+    }
+    static_for<KS>([&](auto G) {
+      constexpr int g = G, c = g & 1;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (FE && T * KS + g < 2 * TT::PER + 1) fetch(std::integral_constant<int, T * KS + g>{});
+      // the next group's fragments
+      if constexpr (SC && g + 1 < KS) {
+        fq[c ^ 1] = frag_rows<HD>(Qr, T * 32, (g + 1) * 16);
+        fd[c ^ 1] = frag_rows<HD>(Dr, T * 32, (g + 1) * 16);
+      }
+      if constexpr (PV && g + 1 < KS) {
+        fc[2 * (c ^ 1)] = cfrag(std::integral_constant<int, (2 * g + 2) % 16>{});
+        fc[2 * (c ^ 1) + 1] = cfrag(std::integral_constant<int, (2 * g + 3) % 16>{});
+      }
+      if constexpr (SM && g % 2 == 1 && g + 1 < KS) {
+        l4[(g + 1) / 2 % 2] = *reinterpret_cast<const f32x4*>(Ls + 4 * (g + 1));
+        d4[(g + 1) / 2 % 2] = *reinterpret_cast<const f32x4*>(Dl + 4 * (g + 1));
+      }
+      // four MFMAs, each followed by a quarter of the vector work: a wave issues in order, and an MFMA
+      // directly behind another waits for it, with everything after
+      constexpr int e0 = 2 * g, e1 = e0 + 1, lb = g / 2 % 2;
+      float x0, x1, y0, y1;
+      if constexpr (SC) s[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[c], kf[g], s[T], 0, 0, 0);
+      if constexpr (SM) {
+        x0 = __builtin_fmaf(s[U][e0], sl2, -l4[lb][e0 % 4] * LOG2E);
+        x1 = __builtin_fmaf(s[U][e1], sl2, -l4[lb][e1 % 4] * LOG2E);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (PV) mfma_acc<!SC>(dv[g % DT], fc[2 * c], pb[T][g / DT]);
+      if constexpr (SM) {
+        x0 = fast_exp2(x0);
+        x1 = fast_exp2(x1);
+        pin(x0, x1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (SC) dp[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fd[c], vf[g], dp[T], 0, 0, 0);
+      if constexpr (SM) {
+        y0 = dp[U][e0] - d4[lb][e0 % 4];
+        y1 = dp[U][e1] - d4[lb][e1 % 4];
+        x0 = lo <= 8 * (e0 / 4) + e0 % 4 ? x0 : 0.f;
+        x1 = lo <= 8 * (e1 / 4) + e1 % 4 ? x1 : 0.f;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (PV) mfma_acc<!SC>(dk[g % DT], fc[2 * c + 1], sb[T][g / DT]);
+      if constexpr (SM) {
+        s[U][e0] = x0;
+        s[U][e1] = x1;
+        dp[U][e0] = x0 * y0;
+        dp[U][e1] = x1 * y1;
+        if constexpr (g == 3) { pb[U][0] = acc_rows_to_b<0>(s[U]); sb[U][0] = acc_rows_to_b<0>(dp[U]); }
+        if constexpr (g == 7) { pb[U][1] = acc_rows_to_b<8>(s[U]); sb[U][1] = acc_rows_to_b<8>(dp[U]); }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  constexpr std::integral_constant<int, 0> t0{};
+  constexpr std::integral_constant<int, 1> t1{};
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  auto arrive = [&] {
+    wait_vm_lds<0>();
+    block_barrier();  // every thread's loads of the stage are in; every wave is done with the last iteration
+  };
+  if (it0 < nit) {
+    ranges();
+    static_for<2 * TT::PER + 1>(fetch);
+    const bf16 *cur = ring, *prev;
+    int qc = f.q0, qp;  // first queries of the stages cur and prev
+    auto turn = [&] {   // the stage just loaded becomes cur
+      prev = cur;
+      qp = qc;
+      cur = ring + f.slot * D::SSZ;
+      qc = f.q0;
+    };
+    arrive();
+    next_tile();
+    step(t0, yes, no, no, yes, cur, cur, 0, cur);
+    step(t1, yes, yes, no, yes, cur, cur, qc, cur);
+    for (int it = it0 + 1; it < nit; ++it) {
+      turn();
+      arrive();
+      next_tile();  // into the stage before prev
+      step(t0, yes, yes, yes, yes, cur, prev, qp + 32, prev);
+      step(t1, yes, yes, yes, yes, cur, cur, qc, prev);
+    }
+    acc_settled(dk, dv);
+    step(t0, no, yes, yes, no, cur, cur, qc + 32, cur);
+    step(t1, no, no, yes, no, cur, cur, 0, cur);
+    acc_settled(dk, dv);
+    wait_vm_lds<0>();  // the last, unread loads: the ring becomes the output staging
+  }
+  block_barrier();  // every wave is done with the last stage: the ring becomes the output staging
+  float* out_stage = reinterpret_cast<float*>(smem);
+  if (a.nsplit > 1) {
+    const int kvd = a.Hkv * HD;
+    float* p = a.part + ((int64_t)split * 2 * a.B + b) * a.S * kvd + kvh * HD;
+    store_partial_from_t<HD>(out_stage, dk, p, kvd, kbk * QB, a.S);
+    store_partial_from_t<HD>(out_stage, dv, p + (int64_t)a.B * a.S * kvd, kvd, kbk * QB, a.S);
+    return;
+  }
+  bf16* outb = (bf16*)a.dqkv + (int64_t)b * a.S * ld;
+  store_rows_from_t<HD>(out_stage, dk, 1.0f / sqrtf((float)HD), outb + (a.Hq + kvh) * HD, ld, kbk * QB, a.S,
+                        a.rope_cos, a.rope_sin);
+  store_rows_from_t<HD>(out_stage, dv, 1.0f, outb + (a.Hq + a.Hkv + kvh) * HD, ld, kbk * QB, a.S);
+}
+
+__global__ void __launch_bounds__(NT) flash_bwd_dkv128(AttnArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int nkb = (a.S + QB - 1) / QB;
   int unit, idx;  // unit: (batch, key/value head); low key blocks (the most queries) first
   xcd_item(blockIdx.x, nkb * a.nsplit * a.Hkv * a.B, nkb * a.nsplit, unit, idx);
-  bwd_dkv_block<HD>(a, idx / a.nsplit, idx % a.nsplit, unit % a.Hkv, unit / a.Hkv, smem);
+  bwd_dkv128_block(a, idx / a.nsplit, idx % a.nsplit, unit % a.Hkv, unit / a.Hkv, smem);
 }
 
 // dQ and dK/dV work items in one launch (independent given delta), so the two fill the CUs
@@ -929,7 +1104,7 @@ void bwd_launch(const AttnArgs& args, hipStream_t st) {
   static bool attr = false;
   if (!attr) {
     set_lds(flash_bwd_dq<HD>, Lds<HD>::dq_bytes());
-    set_lds(flash_bwd_dkv<HD>, Lds<HD>::dkv_bytes());
+    set_lds(flash_bwd_dkv128, Dkv128::bytes);
     attr = true;
   }
   if (!a.delta_ready) {  // rowsum(dO O), from O in fp32 when the forward kept it
@@ -944,7 +1119,7 @@ void bwd_launch(const AttnArgs& args, hipStream_t st) {
     flash_bwd_fused<HD><<<(unsigned)(nb * (a.Hq + a.nsplit * a.Hkv) * a.B), NT, bytes, st>>>(a);
   } else {
     flash_bwd_dq<HD><<<(unsigned)(cdiv(a.S, QB) * a.Hq * a.B), NT, Lds<HD>::dq_bytes(), st>>>(a);
-    flash_bwd_dkv<HD><<<(unsigned)(cdiv(a.S, QB) * a.nsplit * a.Hkv * a.B), NT, Lds<HD>::dkv_bytes(), st>>>(a);
+    flash_bwd_dkv128<<<(unsigned)(cdiv(a.S, QB) * a.nsplit * a.Hkv * a.B), NT, Dkv128::bytes, st>>>(a);
   }
   if (a.nsplit > 1)
     dkv_reduce<HD><<<(unsigned)cdiv(2 * (int64_t)a.B * a.S * a.Hkv * HD / 8, 256), 256, 0, st>>>(a);

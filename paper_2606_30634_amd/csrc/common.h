@@ -116,6 +116,9 @@ __device__ __forceinline__ u32x4 buffer_range(const void* base, const void* end)
 __device__ __forceinline__ void dma16_range(u32x4 range, uint32_t voff, uint32_t lds) {
   asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(range), "{m0}"(lds) : "memory");
 }
+__device__ __forceinline__ void dma4_range(u32x4 range, uint32_t voff, uint32_t lds) {
+  asm volatile("buffer_load_dword %0, %1, 0 offen lds" ::"v"(voff), "s"(range), "{m0}"(lds) : "memory");
+}
 
 __device__ __forceinline__ void block_barrier() {
   asm volatile("" ::: "memory");
