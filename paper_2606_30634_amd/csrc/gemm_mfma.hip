@@ -357,7 +357,7 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM
 //     BKT/8)), so the 16 rows one 16-lane group reads for a fragment cover all 64 banks;
 //   row-contiguous tile [BKT][ROWS]: chunk rc of k-row k sits at k * ROWS/8 + (rc ^ 4 (k mod 4)), so
 //     the 4 k-rows x 32 rows of one half-wave transposing read fall in 4 different 64-byte bank
-//     groups (ROWS >= 128, a whole number of 256-byte bank periods per k-row).
+//     groups (ROWS 128 or 256: whole 256-byte bank periods per k-row; ROWS 192: 4 (k / 2 mod 2)).
 // RAG: any M, N, K (the same pipeline; whole products keep the kernels without ranges and predicates,
 // whose epilogue stores need not be waited for).  It replaced a register-staged kernel (M, N, K
 // multiples of 8) and, for the rest, an fp32 FMA tiling: T = 2331 tokens, d 1024, d_ffn 2816, a
@@ -375,7 +375,10 @@ struct DmaTile {
   static constexpr int PER = CHUNKS / NT;  // loads per thread and slice
   static constexpr int ELEMS = ROWS * BKT;
   static_assert(CHUNKS % NT == 0, "tile does not split evenly over the threads");
-  static_assert(KMAJ || ROWS >= 128, "row-contiguous swizzle needs 256-byte k-rows");
+  static_assert(KMAJ || ROWS == 128 || ROWS == 192 || ROWS == 256, "row-contiguous swizzle");
+  // row-contiguous tile: the XOR of k-row k's chunks (k-rows of an odd number of 128 bytes alternate
+  // between the bank halves by themselves)
+  __device__ static int swz(int k) { return ROWS % 128 == 0 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); }
   // k-contiguous tile: the row and the 8-element k chunk whose data LDS chunk p holds
   __device__ static void row_chunk(int p, int& r, int& kc) {
     constexpr int CPR = BKT / 8, RPB = 128 / BKT;
@@ -390,7 +393,7 @@ struct DmaTile {
       return (int64_t)r * ld + kc * 8;
     } else {
       constexpr int CPK = ROWS / 8;
-      const int k = p / CPK, rc = (p % CPK) ^ (4 * (k & 3));
+      const int k = p / CPK, rc = (p % CPK) ^ swz(k);
       return (int64_t)k * ld + rc * 8;
     }
   }
@@ -405,7 +408,7 @@ struct DmaTile {
       const int gq = l / 16, i = l % 16;
       const int r = r0 + 16 * (gq & 1) + 4 * (i & 3);
       const int k = k0 + 8 * (gq >> 1) + (i >> 2);  // k and k + 4 share k mod 4
-      const int col = (((r >> 3) ^ (4 * (k & 3))) << 3) + (r & 7);
+      const int col = (((r >> 3) ^ swz(k)) << 3) + (r & 7);
       typedef __attribute__((address_space(3))) v4i16_t lds_v4i16;
       const v4i16_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(T + k * ROWS + col));
       const v4i16_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(T + (k + 4) * ROWS + col));
@@ -475,11 +478,13 @@ gemm_dma_kernel(GemmArgs g) {
   extern __shared__ __align__(16) unsigned char smem[];
   bf16* S = reinterpret_cast<bf16*>(smem);  // [NS][A tile | B tile]
 
-  const int tiles = !RAG && g.sym ? (g.M / BM) * (g.M / BM + 1) / 2
-                                  : ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  const bool sym = !RAG && BM == BN && g.sym;
+  const int tiles = sym ? (g.M / BM) * (g.M / BM + 1) / 2 : ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   auto origin = [&](int b, int& m0_, int& n0_) {
-    if (!RAG && g.sym) tri_origin<BM, BN>(g, b, m0_, n0_);
-    else tile_origin<BM, BN>(g, b, m0_, n0_);
+    if constexpr (BM == BN) {
+      if (sym) return tri_origin<BM, BN>(g, b, m0_, n0_);
+    }
+    tile_origin<BM, BN>(g, b, m0_, n0_);
   };
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
@@ -725,13 +730,26 @@ bool launch_dma(const GemmArgs& g, hipStream_t st) {
                    : launch_dma_cfg<BM, BN, WM, WN, bf16, BKT, 2, RAG>(g, st);
 }
 
-// Tile choice: 256 x 256 (8 waves of 64 x 128, 64-deep slices in 2 stages) when the product has
-// enough of them and is deep enough for the larger tile to pay (at K = 768 the persistent
-// 128 x 128 kernel is faster, from K = 1536 on the 256 x 256 one), else 128 x 128.
-constexpr int BIG_K = 1536;
+// Tile choice: 256 x 256 (8 waves of 64 x 128, 64-deep slices in 2 stages, one block per CU) when the
+// product has enough of them and is deep enough for the larger tile to pay, else 128 x 128 (two blocks
+// per CU).  From K = 768 it pays where its rounds of 256 tiles are nearly full (M 8192, K 768, N 6144: 3
+// rounds, 109 -> 91 us; N 49152: 700 -> 646; N 3072, 1.5 rounds: 69 -> 80 us), from K = 1536 on anyway.
 bool use_big(const GemmArgs& g) {
-  const int64_t t256 = cdiv(g.M, 256) * cdiv(g.N, 256);
-  return g.K >= BIG_K && (t256 >= 512 || (t256 >= 256 && g.K >= 2048));
+  const int64_t t256 = cdiv(g.M, 256) * cdiv(g.N, 256), rounds = cdiv(t256, 256);
+  return (g.K >= 768 && t256 >= 512 && 10 * t256 >= 9 * 256 * rounds) ||
+         (g.K >= 1536 && (t256 >= 512 || (t256 >= 256 && g.K >= 2048)));
+}
+
+// Weight-gradient products (fp32, row-contiguous operands) whose 128 x 128 blocks just miss a round of
+// the 512 the chip holds: 128 x 192 tiles (4 waves of 64 x 96, two blocks per CU) when they need fewer
+// rounds by more than their size (8 % more work per unit of time by fewer operand bytes).  K 8192, 768 x
+// 3072 in 4 splits, 576 -> 384 blocks: 71 -> 53 us; 6144 x 768 in 2: 121 -> 85 us; 768 x 768 in 8, one
+// round either way: 26.3 against 27.0 us.
+bool use_wide(const GemmArgs& g) {
+  if (!g.out_f32 || g.a_kmajor || g.b_kmajor || g.M % 128 || g.N % 192 || g.K % BKT) return false;
+  const int64_t r128 = cdiv(cdiv(g.M, 128) * cdiv(g.N, 128) * g.ksplit, 512);
+  const int64_t r192 = cdiv((int64_t)(g.M / 128) * (g.N / 192) * g.ksplit, 512);
+  return 138 * r192 < 100 * r128;
 }
 
 // What every direct-to-LDS kernel needs: 16-byte aligned operand rows (a k-contiguous operand of
@@ -818,7 +836,10 @@ bool gemm_mfma_try(const GemmArgs& g0, hipStream_t st) {
                      (g.N | g.ldc) % 4 == 0;
   bool done;
   if (big) done = whole ? launch_dma<256, 256, 64, 128, false>(g, st) : launch_dma<256, 256, 64, 128, true>(g, st);
-  else done = whole ? launch_dma<128, 128, 64, 64, false>(g, st) : launch_dma<128, 128, 64, 64, true>(g, st);
+  else if (whole && use_wide(g)) {
+    launch_dma_one<128, 192, 64, 96, false, false, float, BKT, 2, EPI_PLAIN, false>(g, (g.M / 128) * (g.N / 192), st);
+    done = true;
+  } else done = whole ? launch_dma<128, 128, 64, 64, false>(g, st) : launch_dma<128, 128, 64, 64, true>(g, st);
   if (!done) return false;
   if (g.ksplit > 1)
     splitk_reduce<<<(unsigned)cdiv(cdiv(mn, 4), 256), 256, 0, st>>>(g.ws, g.ksplit, mn, (float*)g.C, g.beta);
