@@ -95,7 +95,8 @@ void launch_mean(const float* v, int n, float* out, hipStream_t st);
 // out_f32: C is fp32 (beta 0: overwrite, 1: accumulate); else C has the input type.
 // resid (input type, leading dimension ldc) is added when non-null.
 // ws / ws_elems: optional fp32 workspace; when the output tile grid underfills the chip and K is
-// long, an fp32-output product is split over K into partial tiles there and summed in a fixed order.
+// long, a product (fp32 output; bf16 output without a fused epilogue) is split over K into partial
+// tiles there and summed in a fixed order.
 struct GemmArgs {
   int M, N, K;
   const void* A; int lda; bool a_kmajor;

@@ -139,6 +139,8 @@ struct stage {
   float *delta, *rms_part, *row_loss, *cos_t, *sin_t, *norm_out, *upd_norm_out;
   double *norm_part, *upd_norm_part;
   float* gemm_ws;
+  float* act_ws;  // split-K partials of the [T, d_model] activation products (null: none are split)
+  int64_t act_ws_elems = 0;
   float* attn_part;  // partial dk, dv of the attention backward's split items (null: none are split)
   int* flag;
   unsigned long long* skipped;
@@ -245,11 +247,11 @@ void flush_pending(stage* S) {
   while (!S->pend.chunks.empty()) launch_pending_chunk(S);
 }
 
-// activation products on the stage stream (no split-K: the workspace belongs to the
-// weight-gradient stream)
+// activation products on the stage stream (split-K partials in a workspace of their own: gemm_ws
+// belongs to the weight-gradient stream)
 void run_gemm(stage* S, GemmArgs g) {
-  g.ws = nullptr;
-  g.ws_elems = 0;
+  g.ws = g.out_f32 ? nullptr : S->act_ws;
+  g.ws_elems = g.out_f32 ? 0 : S->act_ws_elems;
   timed(S, STAGE_PROF_GEMM, 2.0 * g.M * g.N * g.K, [&] { launch_gemm(S->bf, g, S->st); });
 }
 
@@ -399,6 +401,10 @@ size_t layout(stage* S, char* base) {
   S->upd_norm_part = (double*)carve(norm_scratch_bytes());
   S->upd_norm_out = (float*)carve(2 * 4);
   S->gemm_ws = sh.dtype == 1 ? (float*)carve(GEMM_WS_ELEMS * 4) : nullptr;
+  // at most 512 tiles of 128 x 128 of partials, for products of at most half as many
+  S->act_ws_elems = sh.dtype == 1 && cdiv(T, 128) * cdiv(d, 128) <= 256
+      ? std::min<int64_t>(8, 512 / (cdiv(T, 128) * cdiv(d, 128))) * T * d : 0;
+  S->act_ws = S->act_ws_elems ? (float*)carve(S->act_ws_elems * 4) : nullptr;
   const int64_t part = sh.dtype == 1
       ? attention_part_elems(sh.micro_batch, sh.seq_len, sh.n_heads, sh.n_kv_heads, sh.head_dim) : 0;
   S->attn_part = part ? (float*)carve(part * 4) : nullptr;
