@@ -110,18 +110,20 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd(const T* __restrict__ dn, con
   }
 }
 
-// Fixed-order column sums of a [nrows][d] fp32 array, one level of a two-level tree: thread j of
-// group g sums rows [g G, min(g G + G, nrows)) of column j in row order and writes dst[g][j]
-// (dst (+)= when accumulate, used for the last level whose single group covers every row).
-__global__ void __launch_bounds__(256) colsum_rows(const float* __restrict__ src, int nrows, int d, int G,
-                                                   float* __restrict__ dst, int accumulate) {
+// Fixed-order column sums of [nrows][d] fp32 arrays (array blockIdx.z at src + z stride), one level of
+// a two-level tree: thread j of group g sums rows [g G, min(g G + G, nrows)) of column j in row order
+// and writes dst[g][j] (dst (+)= when accumulate, used for the last level whose single group covers
+// every row).
+__global__ void __launch_bounds__(256) colsum_rows(const float* __restrict__ src, int64_t stride, int nrows, int d,
+                                                   int G, ColsumOut dst, int accumulate) {
   const int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= d) return;
+  src += blockIdx.z * stride;
   const int r0 = blockIdx.y * G, r1 = min(nrows, r0 + G);
   float s = 0.f;
 #pragma unroll 8
   for (int r = r0; r < r1; ++r) s += src[(int64_t)r * d + j];
-  float* o = dst + (int64_t)blockIdx.y * d + j;
+  float* o = dst.p[blockIdx.z] + (int64_t)blockIdx.y * d + j;
   *o = accumulate ? *o + s : s;
 }
 
@@ -504,6 +506,39 @@ __global__ void __launch_bounds__(64) radix_scatter(const int32_t* __restrict__ 
   }
 }
 
+// Few positions: the whole sort in one block, one launch in place of the nine above.  The keys are
+// token << 13 | position (30 bits), all different, so a bitonic network in LDS sorts them stably.  A
+// wave's 64 pairs span 128 consecutive keys while the partner distance is at most 64: those steps need no
+// barrier between the waves.  N: the power of two >= n, n <= SORT_ONE.
+constexpr int SORT_ONE = 8192;
+__global__ void __launch_bounds__(1024) token_sort_one(const int32_t* __restrict__ tok, int n, int N, int vocab,
+                                                       uint32_t* __restrict__ sorted_tok,
+                                                       uint32_t* __restrict__ sorted_pos) {
+  extern __shared__ uint32_t key[];
+  for (int i = threadIdx.x; i < N; i += blockDim.x)
+    key[i] = i < n ? token_key(tok, i, vocab) << 13 | (uint32_t)i : 0xffffffffu;
+  __syncthreads();
+  for (int k = 2; k <= N; k <<= 1) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int t = threadIdx.x; t < N / 2; t += blockDim.x) {
+        const int a = 2 * j * (t / j) + t % j, b = a + j;
+        const uint32_t x = key[a], y = key[b];
+        const bool up = (a & k) == 0;
+        key[a] = up ? min(x, y) : max(x, y);
+        key[b] = up ? max(x, y) : min(x, y);
+      }
+      // the next step's pairs cross waves if this step's or its own distance exceeds 64
+      if (j > 64 || (j == 1 && k >= 128)) __syncthreads();
+      else __builtin_amdgcn_wave_barrier();
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    sorted_tok[i] = key[i] >> 13;
+    sorted_pos[i] = key[i] & 8191u;
+  }
+}
+
 // row_start[v] = first sorted index with token >= v (binary search over the sorted tokens), v in [0, vocab]
 __global__ void __launch_bounds__(256) token_row_start(const uint32_t* __restrict__ sorted_tok, int n,
                                                        int vocab, int32_t* __restrict__ row_start) {
@@ -748,18 +783,21 @@ int launch_rmsnorm_bwd(bool bf, const void* dn, const void* x, const float* rstd
             : rmsb_t<float>(dn, x, rstd, gamma, resid, dx, partial, rows, d, st);
 }
 
-void launch_colsum_partials(float* partial, int nchunks, int d, float* out, bool accumulate,
-                            hipStream_t st) {
-  const unsigned cb = (unsigned)cdiv(d, 256);
+void launch_colsum_partials(float* partial, int64_t stride, int count, int nchunks, int d, const ColsumOut& out,
+                            bool accumulate, hipStream_t st) {
+  if (count == 0) return;
+  const unsigned cb = (unsigned)cdiv(d, 256), nz = (unsigned)count;
   if (nchunks <= 32) {
-    colsum_rows<<<dim3(cb, 1), 256, 0, st>>>(partial, nchunks, d, nchunks, out, accumulate ? 1 : 0);
+    colsum_rows<<<dim3(cb, 1, nz), 256, 0, st>>>(partial, stride, nchunks, d, nchunks, out, accumulate ? 1 : 0);
     return;
   }
   constexpr int G = 16;  // rows per first-level group; the group sums go after the partial rows
   const int n1 = cdiv(nchunks, G);
   float* tmp = partial + (int64_t)nchunks * d;
-  colsum_rows<<<dim3(cb, (unsigned)n1), 256, 0, st>>>(partial, nchunks, d, G, tmp, 0);
-  colsum_rows<<<dim3(cb, 1), 256, 0, st>>>(tmp, n1, d, n1, out, accumulate ? 1 : 0);
+  ColsumOut groups;
+  for (int k = 0; k < count; ++k) groups.p[k] = tmp + k * stride;
+  colsum_rows<<<dim3(cb, (unsigned)n1, nz), 256, 0, st>>>(partial, stride, nchunks, d, G, groups, 0);
+  colsum_rows<<<dim3(cb, 1, nz), 256, 0, st>>>(tmp, stride, n1, d, n1, out, accumulate ? 1 : 0);
 }
 
 template <typename T>
@@ -785,6 +823,12 @@ int64_t token_sort_ws_elems(int n) { return 2 * (int64_t)n + (int64_t)RADIX_DIG 
 void launch_token_sort(const int32_t* tok, int n, int vocab, int32_t* ws, uint32_t* sorted_tok,
                        uint32_t* sorted_pos, hipStream_t st) {
   if (n <= 0) return;
+  if (n <= SORT_ONE) {
+    int N = 2;
+    while (N < n) N <<= 1;
+    token_sort_one<<<1, std::min(1024, std::max(64, N / 2)), N * 4, st>>>(tok, n, N, vocab, sorted_tok, sorted_pos);
+    return;
+  }
   const int nchunk = (int)cdiv(n, RADIX_CHUNK);
   uint32_t* tk = reinterpret_cast<uint32_t*>(ws);  // the ping-pong partner of (sorted_tok, sorted_pos)
   uint32_t* tv = tk + n;

@@ -53,10 +53,12 @@ constexpr int RMS_CHUNK = 32;
 int launch_rmsnorm_bwd(bool bf, const void* dn, const void* x, const float* rstd,
                         const void* gamma, const void* resid, void* dx, float* partial, int rows,
                         int d, hipStream_t st);
-// out (+)= the column sums of partial[0 .. nchunks), summed in a fixed order; the rows after
-// them are scratch for the first level of the sum.
-void launch_colsum_partials(float* partial, int nchunks, int d, float* out, bool accumulate,
-                            hipStream_t st);
+// out.p[k] (+)= the column sums of the nchunks rows at partial + k stride, k < count, each summed in a
+// fixed order; the rows after them are scratch for the first level of the sum.
+constexpr int COLSUM_MAX = 8;
+struct ColsumOut { float* p[COLSUM_MAX]; };
+void launch_colsum_partials(float* partial, int64_t stride, int count, int nchunks, int d, const ColsumOut& out,
+                            bool accumulate, hipStream_t st);
 // rows of d floats the partial buffer of launch_rmsnorm_bwd + launch_colsum_partials needs
 inline int64_t rms_partial_rows(int rows) {
   const int64_t p = (rows + 15) / 16;

@@ -141,6 +141,11 @@ struct stage {
   float* gemm_ws;
   float* act_ws;  // split-K partials of the [T, d_model] activation products (null: none are split)
   int64_t act_ws_elems = 0;
+  // the norms of the running backward whose dgamma partials (rms_part, rms_stride floats per norm) are
+  // still to be summed
+  int64_t rms_stride = 0;
+  int colsums = 0, colsum_rows = 0;
+  ColsumOut colsum_out = {};
   float* attn_part;  // partial dk, dv of the attention backward's split items (null: none are split)
   int* flag;
   unsigned long long* skipped;
@@ -396,7 +401,8 @@ size_t layout(stage* S, char* base) {
   S->do_ = carve(T * hqd * esz);
   S->dqkv = carve(T * qkvw * esz);
   S->delta = (float*)carve((int64_t)sh.micro_batch * sh.n_heads * sh.seq_len * 4);
-  S->rms_part = (float*)carve(rms_partial_rows(T) * d * 4);
+  S->rms_stride = rms_partial_rows(T) * d;
+  S->rms_part = (float*)carve(std::min<int64_t>(COLSUM_MAX, 2 * sh.n_blocks + 1) * S->rms_stride * 4);
   S->norm_part = (double*)carve(norm_scratch_bytes());
   S->upd_norm_part = (double*)carve(norm_scratch_bytes());
   S->upd_norm_out = (float*)carve(2 * 4);
@@ -616,6 +622,22 @@ void block_forward(stage* S, int vi, BlockAct& b, const BlockOff& w, void* y) {
   run_gemm(S, gemm(T, d, f, b.z, f, true, S->wptr(vi, w.wdown), f, true, y, d, false, 0.f, b.h));
 }
 
+// The norms' dgamma: launch_rmsnorm_bwd leaves partial rows, summed for up to COLSUM_MAX norms at a time
+// (a sum is two launches of a few microseconds each, whatever the number of norms in it).
+void flush_colsums(stage* S, bool first) {
+  launch_colsum_partials(S->rms_part, S->rms_stride, S->colsums, S->colsum_rows, S->sh.d_model, S->colsum_out, !first,
+                         S->st);
+  S->colsums = 0;
+}
+
+void norm_backward(stage* S, const void* dn, const void* x, const float* rstd, const void* gamma, const void* resid,
+                   void* dx, float* dgamma, bool first) {
+  if (S->colsums == COLSUM_MAX) flush_colsums(S, first);
+  S->colsum_rows = launch_rmsnorm_bwd(S->bf, dn, x, rstd, gamma, resid, dx, S->rms_part + S->colsums * S->rms_stride,
+                                      S->T, S->sh.d_model, S->st);
+  S->colsum_out.p[S->colsums++] = dgamma;
+}
+
 // dy: gradient of the block output; writes the gradient of the block input into dx.
 void block_backward(stage* S, int vi, BlockAct& b, const BlockOff& w, const void* dy, void* dx,
                     float* g, bool first) {
@@ -639,8 +661,7 @@ void block_backward(stage* S, int vi, BlockAct& b, const BlockOff& w, const void
   run_gemm(S, gemm(T, d, 2 * f, S->dgu, 2 * f, true, S->wptr(vi, w.wgu), d, false, S->dn, d));
   run_wgrad(S, gemm(2 * f, d, T, S->dgu, 2 * f, false, b.n2, d, false, g + w.wgu, d, true, beta), WG_GU);
   after_wgrad(S, WG_O);
-  int np = launch_rmsnorm_bwd(bf, S->dn, b.h, b.rstd2, S->wptr(vi, w.ffn_norm), dy, S->dh, S->rms_part, T, d, st);
-  launch_colsum_partials(S->rms_part, np, d, g + w.ffn_norm, !first, st);
+  norm_backward(S, S->dn, b.h, b.rstd2, S->wptr(vi, w.ffn_norm), dy, S->dh, g + w.ffn_norm, first);
   // output projection: do = dh Wo ; dWo (+)= dh^T o.  The attention backward's delta = rowsum(do o)
   // in the product's epilogue, from o in fp32 (the bf16 stage's forward keeps an fp32 copy whose P V
   // product took P as a hi / lo pair: delta then matches the P and dP the backward recomputes, where
@@ -671,8 +692,7 @@ void block_backward(stage* S, int vi, BlockAct& b, const BlockOff& w, const void
   run_gemm(S, gemm(T, d, S->qkvw, S->dqkv, S->qkvw, true, S->wptr(vi, w.wqkv), d, false, S->dn, d));
   run_wgrad(S, gemm(S->qkvw, d, T, S->dqkv, S->qkvw, false, b.n1, d, false, g + w.wqkv, d, true, beta), WG_QKV);
   after_wgrad(S, WG_DOWN);  // dx is the buffer the next-higher block's down-projection product read
-  np = launch_rmsnorm_bwd(bf, S->dn, b.x, b.rstd1, S->wptr(vi, w.attn_norm), S->dh, dx, S->rms_part, T, d, st);
-  launch_colsum_partials(S->rms_part, np, d, g + w.attn_norm, !first, st);
+  norm_backward(S, S->dn, b.x, b.rstd1, S->wptr(vi, w.attn_norm), S->dh, dx, g + w.attn_norm, first);
 }
 
 }  // namespace
@@ -913,6 +933,7 @@ int stage_backward(stage_t* s, int32_t slot, const void* dy, void* dx_out, int32
   hipStream_t st = s->st;
   const void* cur = dy;
   bool head_wrote_embed = false;
+  s->colsums = 0;
   if (sh.last_stage) {
     launch_ce_bwd(bf, sl.logits, sl.targets, sl.lse_ce, T, sh.vocab, 1.0f / ((float)T * microbatches_per_step),
                   s->dlog, s->lddlog, st);
@@ -925,9 +946,7 @@ int stage_backward(stage_t* s, int32_t slot, const void* dy, void* dx_out, int32
     gw.a_padded = true;
     run_wgrad(s, gw, WG_HEAD);
     head_wrote_embed = s->off_head == s->off_embed;
-    const int np = launch_rmsnorm_bwd(bf, s->dhf, sl.y, sl.rstdf, s->wptr(vi, s->off_final), nullptr, s->dA,
-                                       s->rms_part, T, d, st);
-    launch_colsum_partials(s->rms_part, np, d, g + s->off_final, !first, st);
+    norm_backward(s, s->dhf, sl.y, sl.rstdf, s->wptr(vi, s->off_final), nullptr, s->dA, g + s->off_final, first);
     cur = s->dA;
   }
   for (int i = sh.n_blocks - 1; i >= 0; --i) {
@@ -947,6 +966,7 @@ int stage_backward(stage_t* s, int32_t slot, const void* dy, void* dx_out, int32
   } else if (dx_out) {
     HIP_OK(hipMemcpyAsync(dx_out, cur, (size_t)T * d * s->esz, hipMemcpyDeviceToDevice, st));
   }
+  flush_colsums(s, first);
   join_wgrad(s);  // every weight gradient is in g
   HIP_OK(hipEventRecord(s->ev_bwd[vi], st));
   s->ev_bwd_set[vi] = true;
