@@ -138,7 +138,7 @@ __device__ __forceinline__ float sigmoid(float a) {
 // waited for here.  The staging area (waves x RP x (WN + 4) floats) must be free.
 template <int BM, int BN, int WM, int WN, typename OutT, int EPI, int RP, bool RAG>
 __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM / 32][WN / 32],
-                                             float* stage, int m0, int n0, int wm0, int wn0) {
+                                             float* stage, int m0, int n0, int wm0, int wn0, int tail) {
   static_assert(RP == 16 || RP == 8, "staging part of 8 or 16 rows");
   static_assert(sizeof(OutT) == 2 || EPI == EPI_PLAIN, "fp32 output has no fused epilogue");
   constexpr int FM = WM / 32, FN = WN / 32;
@@ -160,7 +160,13 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   float* stg = stage + wave * RP * EP;
   const bool split = sizeof(OutT) == 4 && g.ksplit > 1;
-  float* W = split ? g.ws + (int64_t)blockIdx.y * g.M * g.N : nullptr;
+  // partial sums: whole [M, N] arrays, or BM x BN tiles when only a range of tiles is split (W and ldw
+  // such that C's row and column index both)
+  const bool range = split && g.tile_n > 0;
+  const int ldw = range ? BN : g.N;
+  float* W = !split ? nullptr
+             : range ? g.ws + ((int64_t)blockIdx.y * g.tile_n + tail) * BM * BN - ((int64_t)m0 * BN + n0)
+                     : g.ws + (int64_t)blockIdx.y * g.M * g.N;
   // output chunk j of part p of this lane: staged row r, column cc; C row, column
   auto chunk = [&](int p, int j, int& r, int& cc, int& row, int& col) {
     const int c = lane + 64 * j;
@@ -205,14 +211,14 @@ __device__ __forceinline__ void dma_epilogue(const GemmArgs& g, f32x16 (&acc)[WM
         if (RAG && (g.N | (split ? 0 : g.ldc)) % 4 != 0) {
           for (int q = 0; q < 4 && col + q < g.N; ++q) {
             if (split) {
-              W[(int64_t)row * g.N + col + q] = v[q];
+              W[(int64_t)row * ldw + col + q] = v[q];
             } else {
               float* c = (float*)g.C + (int64_t)row * g.ldc + col + q;
               *c = g.beta != 0.f ? v[q] + g.beta * *c : v[q];
             }
           }
         } else if (split) {
-          st_nt(W + (int64_t)row * g.N + col, make_float4(v[0], v[1], v[2], v[3]));
+          st_nt(W + (int64_t)row * ldw + col, make_float4(v[0], v[1], v[2], v[3]));
         } else {
           float* Cf = (float*)g.C + (int64_t)row * g.ldc + col;
           if (g.beta != 0.f) {
@@ -447,7 +453,7 @@ constexpr int dma_waves_per_simd() {
   return w > 8 ? 8 : (w < 1 ? 1 : w);
 }
 
-// Block b takes tiles b, b + gridDim.x, ... (gridDim.x a multiple of 8 when it is below the tile
+// Block b takes tiles b, b + gridDim.x, ... of the launch's range (tile0 a multiple of 8, gridDim.x a multiple of 8 when it is below the tile
 // count, so that every tile of a block maps to the block's XCD).  The slices of all its tiles form
 // one sequence: the loads of slice G + NS - 1 of that sequence (the next tile's first slices near
 // the end of a tile) are issued while slice G is consumed, into stage (G + NS - 1) mod NS.
@@ -552,7 +558,8 @@ gemm_dma_kernel(GemmArgs g) {
     }
   };
 
-  int t = blockIdx.x;
+  const int tile_end = g.tile_n > 0 ? g.tile0 + g.tile_n : tiles;
+  int t = g.tile0 + blockIdx.x;
   int m0, n0;
   origin(t, m0, n0);
   const bf16* at = a_tile(m0);
@@ -564,7 +571,7 @@ gemm_dma_kernel(GemmArgs g) {
   int G = 0;  // position in the block's slice sequence
   for (bool first = true;; first = false) {
     const int tn = t + gridDim.x;
-    const bool next = chain && tn < tiles;
+    const bool next = chain && tn < tile_end;
     int m1 = m0, n1 = n0;
     if (next) origin(tn, m1, n1);
     const bf16* atn = a_tile(m1);
@@ -634,7 +641,7 @@ gemm_dma_kernel(GemmArgs g) {
     }
     wait_vm_lds<63>();
     block_barrier();
-    dma_epilogue<BM, BN, WM, WN, OutT, EPI, C_::RP, RAG>(g, acc, stg, m0, n0, wm0, wn0);
+    dma_epilogue<BM, BN, WM, WN, OutT, EPI, C_::RP, RAG>(g, acc, stg, m0, n0, wm0, wn0, t - g.tile0);
     if (!next) break;
     t = tn; m0 = m1; n0 = n1; at = atn; bt = btn;
   }
@@ -664,6 +671,27 @@ __global__ void __launch_bounds__(256) splitk_reduce(const float* __restrict__ w
       C[k] = beta != 0.f ? acc + beta * C[k] : acc;
     }
   }
+}
+
+// The same for the BM x BN partial tiles of the products' tiles tile0 .. tile0 + tile_n - 1, one block row
+// per tile (whole tiles)
+template <int BM, int BN>
+__global__ void __launch_bounds__(256) splitk_reduce_tiles(GemmArgs g) {
+  int m0, n0;
+  tile_origin<BM, BN>(g, g.tile0 + blockIdx.y, m0, n0);
+  const int e = 4 * (blockIdx.x * 256 + threadIdx.x);
+  const float* w = g.ws + (int64_t)blockIdx.y * BM * BN + e;
+  float4 acc = ld_nt<float4>(w);
+  for (int s = 1; s < g.ksplit; ++s) {
+    const float4 v = ld_nt<float4>(w + (int64_t)s * g.tile_n * BM * BN);
+    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+  }
+  float* c = (float*)g.C + (int64_t)(m0 + e / BN) * g.ldc + n0 + e % BN;
+  if (g.beta != 0.f) {
+    const float4 o = *reinterpret_cast<const float4*>(c);
+    acc.x += g.beta * o.x; acc.y += g.beta * o.y; acc.z += g.beta * o.z; acc.w += g.beta * o.w;
+  }
+  *reinterpret_cast<float4*>(c) = acc;
 }
 
 // C = bf16 of the sum over splits of the partial tiles, in split order, plus resid (all rows of N)
@@ -718,7 +746,8 @@ void launch_dma_one(const GemmArgs& g, int nblk, hipStream_t st) {
 // k-contiguous A (every bf16-output product of the stage has one) with each epilogue kind.
 template <int BM, int BN, int WM, int WN, typename OutT, int BKT, int NS, bool RAG>
 bool launch_dma_cfg(const GemmArgs& g, hipStream_t st) {
-  const int nblk = !RAG && g.sym ? (g.M / BM) * (g.M / BM + 1) / 2 : (int)(cdiv(g.M, BM) * cdiv(g.N, BN));
+  const int nblk = g.tile_n > 0 ? g.tile_n
+                   : !RAG && g.sym ? (g.M / BM) * (g.M / BM + 1) / 2 : (int)(cdiv(g.M, BM) * cdiv(g.N, BN));
 #define L_(AK, BKM, E) launch_dma_one<BM, BN, WM, WN, AK, BKM, OutT, BKT, NS, E, RAG>(g, nblk, st)
   if constexpr (sizeof(OutT) == 4) {
     if (g.a_kmajor && g.b_kmajor) L_(true, true, EPI_PLAIN);
@@ -763,6 +792,9 @@ bool launch_dma(const GemmArgs& g, hipStream_t st) {
 // rounds, 109 -> 91 us; N 49152: 700 -> 646; N 3072, 1.5 rounds: 69 -> 80 us), from K = 1536 on anyway.
 bool use_big(const GemmArgs& g) {
   const int64_t t256 = cdiv(g.M, 256) * cdiv(g.N, 256), rounds = cdiv(t256, 256);
+  // fp32 products of 129-255 tiles: one round, where 128 x 128 tiles take two (K 8192, 2048 x 6144: 201 ->
+  // 176 us)
+  if (g.out_f32 && g.K >= 2048 && g.M % 256 == 0 && g.N % 256 == 0 && t256 > 128 && t256 < 256) return true;
   return (g.K >= 768 && t256 >= 512 && 10 * t256 >= 9 * 256 * rounds) ||
          (g.K >= 1536 && (t256 >= 512 || (t256 >= 256 && g.K >= 2048)));
 }
@@ -789,6 +821,28 @@ int activation_splits(const GemmArgs& g) {
   int s = (int)std::min<int64_t>(8, 512 / tiles);
   while (s > 1 && (s * mn > g.ws_elems || g.K / s < 512 || (s - 1) * cdiv(slices, s) >= slices)) --s;
   return s;
+}
+
+// fp32 products of whole 256 x 256 tiles over more than two rounds of 256: the tiles past the last full
+// round would take a round to themselves at a half or less of the blocks, so they are split over K as far
+// as a round holds them.  K 8192: 4096 x 14336, 768 + 128 tiles, 824 -> 777 us; 49152 x 768, 512 + 64, 624 ->
+// 576 us.  (128 x 128 tiles gain nothing: 2048 x 6144, 512 + 256 tiles, 195 -> 202 us.)
+bool launch_tail_split(const GemmArgs& g, hipStream_t st) {
+  constexpr int B = 256, WM = 64, WN = 128, slots = 256;
+  const int tiles = (g.M / B) * (g.N / B), tail = tiles % slots, slices = g.K / BKT;
+  if (!g.out_f32 || g.ksplit > 1 || !g.ws || tiles < slots || tail == 0 || tail > slots / 2) return false;
+  int s = std::min(8, slots / tail);
+  while (s > 1 && (slices % s || g.K / s < 512 || (int64_t)s * tail * B * B > g.ws_elems)) --s;
+  if (s < 2) return false;
+  GemmArgs p = g;
+  p.tile_n = tiles - tail;
+  if (!launch_dma<B, B, WM, WN, false>(p, st)) return false;
+  p.tile0 = tiles - tail;
+  p.tile_n = tail;
+  p.ksplit = s;
+  if (!launch_dma<B, B, WM, WN, false>(p, st)) return false;
+  splitk_reduce_tiles<B, B><<<dim3(B * B / 1024, tail), 256, 0, st>>>(p);
+  return true;
 }
 
 // What every direct-to-LDS kernel needs: 16-byte aligned operand rows (a k-contiguous operand of
@@ -871,7 +925,7 @@ bool gemm_mfma_try(const GemmArgs& g0, hipStream_t st) {
   if (g.out_f32 && g.ws && g.ldc == g.N && tiles < 512 && g.K >= 2048) {
     // deterministic split-K for underfilled fp32-output products: whole slices per split, equal
     // splits where K is a whole number of slices, none empty otherwise
-    int s = (int)std::min<int64_t>(8, cdiv(512, tiles));
+    int s = big && tiles < 256 ? 1 : (int)std::min<int64_t>(8, cdiv(512, tiles));
     while (s > 1 && (s * mn > g.ws_elems || g.K / s < 512 ||
                      (g.K % BKT == 0 ? slices % s != 0 : (s - 1) * cdiv(slices, s) >= slices)))
       --s;
@@ -884,9 +938,11 @@ bool gemm_mfma_try(const GemmArgs& g0, hipStream_t st) {
   const int bm = big ? 256 : 128;
   const bool whole = g.M % bm == 0 && g.N % bm == 0 && g.K % BKT == 0 && slices % g.ksplit == 0 &&
                      (g.N | g.ldc) % 4 == 0;
+  const bool wide = whole && !big && use_wide(g);
   bool done;
+  if (whole && big && launch_tail_split(g, st)) return true;
   if (big) done = whole ? launch_dma<256, 256, 64, 128, false>(g, st) : launch_dma<256, 256, 64, 128, true>(g, st);
-  else if (whole && use_wide(g)) {
+  else if (wide) {
     launch_dma_one<128, 192, 64, 96, false, false, float, BKT, 2, EPI_PLAIN, false>(g, (g.M / 128) * (g.N / 192), st);
     done = true;
   } else done = whole ? launch_dma<128, 128, 64, 64, false>(g, st) : launch_dma<128, 128, 64, 64, true>(g, st);

@@ -110,6 +110,7 @@ struct GemmArgs {
   const void* resid;
   float* ws = nullptr; int64_t ws_elems = 0;
   int ksplit = 1;  // set by the launcher
+  int tile0 = 0, tile_n = 0;  // set by the launcher: a launch of tiles tile0 .. tile0 + tile_n - 1 only (0: all)
   // epilogue 1 (SwiGLU backward): the product is dz [M, N]; aux holds the saved gate|up
   // pre-activations [M, 2N] (row stride ld_aux) and C receives dgate in columns [0, N) and dup in
   // [N, 2N) (row stride ldc): da = dz b s (1 + a (1 - s)), db = dz a s, s = sigmoid(a).
