@@ -37,6 +37,8 @@ int fail(int code, const std::string& msg) {
 constexpr size_t ALIGN = 256;
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
+constexpr int64_t WGRAD_IN_ORDER = 1 << 17;  // tokens x d_model
+
 struct BlockOff {  // element offsets of one block's weights in the flat parameter vector
   int64_t attn_norm, wqkv, wo, ffn_norm, wgu, wdown;
 };
@@ -116,6 +118,10 @@ struct stage {
   // unit.  Products that fill it gain nothing from a second stream and would only run each other's
   // kernels slower (measured on the large workload: 367 ms per step either way), so they run in
   // order on the stage stream.
+  // Up to WGRAD_IN_ORDER activation elements the host's launches and event calls are the bound, and the
+  // second stream's events are a sixth of them: in order there too (two blocks, fp32: T 128, d 128 408 ->
+  // 344 us, T 256, d 256 422 -> 389; bf16 T 256, d 512 485 -> 455, T 256, d 256 373 -> 378; at twice the
+  // elements bf16 509 -> 492, fp32 719 -> 732).
   hipStream_t wst = nullptr;
   bool wgrad_side = true;
   hipEvent_t ev_m2s = nullptr, ev_wjoin = nullptr, ev_wg[5] = {};
@@ -728,7 +734,8 @@ int stage_init(const stage_shape_t* shape, void* arena, size_t arena_bytes, void
   S->T = shape->seq_len * shape->micro_batch;
   S->qkvw = (shape->n_heads + 2 * shape->n_kv_heads) * shape->head_dim;
   S->hqd = shape->n_heads * shape->head_dim;
-  S->wgrad_side = (int64_t)(S->T / 256) * (shape->d_model / 256) < 2 * (int64_t)device_cu_count();
+  S->wgrad_side = (int64_t)(S->T / 256) * (shape->d_model / 256) < 2 * (int64_t)device_cu_count() &&
+                  (int64_t)S->T * shape->d_model > WGRAD_IN_ORDER;
   const size_t need = layout(S, nullptr);
   if (arena_bytes < need) {
     delete S;
