@@ -1,0 +1,104 @@
+"""Products and passes whose kernel depends on the shape, each against torch in float64 on the GPU from
+the stage's own operands: the tile choices of the weight-gradient products, split activation products,
+the fp32 tilings, and the two token sorts."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _stage(d, ffn, T, bf16=True, blocks=1, vocab=0, first=False, heads=2, hd=64, seed=3):
+    """A middle (or first) stage of one sequence with random weights, in place on the GPU."""
+    import torch
+    from paper_2606_30634_amd.stage import Stage, make_shape
+    st = Stage(make_shape(blocks, d, heads, heads, hd, ffn, vocab, first, False, False, T, 1, 1, bf16=bf16), "cuda:0")
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    st.view("flat.master").normal_(0.0, 0.02, generator=gen)
+    st.resume(0, 0)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    x = torch.randn(1, T, d, generator=gen, device="cuda:0").to(dt)
+    dy = torch.randn(1, T, d, generator=gen, device="cuda:0").to(dt)
+    return st, x, dy
+
+
+def _err(a, b):
+    return float((a.double() - b).norm() / b.norm())
+
+
+# d, ffn, T: dWdown [d, ffn] over K = T
+@pytest.mark.parametrize("d,ffn,T", [
+    (768, 3072, 2048),    # 144 tiles of 128 x 128 in 4 splits just past a round: 128 x 192 tiles
+    (2048, 5632, 2048),   # 176 tiles of 256 x 256: one round of them
+    (4096, 14336, 2048),  # 896 tiles of 256 x 256: the last 128 split over K
+    (768, 3072, 2056),    # the same widths over a ragged K
+], ids=["wide", "one-round", "tail", "ragged"])
+def test_weight_gradient_tiles(d, ffn, T):
+    import torch
+    st, x, dy = _stage(d, ffn, T)
+    out = {}
+    for rep in range(2):  # the second microbatch accumulates
+        st.forward(0, 0, x_in=x, y_out=torch.empty_like(x))
+        st.backward(0, dy=dy, microbatches_per_step=2)
+        torch.cuda.synchronize()
+        out[rep] = st.view("grad0.blk0.wdown").view(d, ffn).clone()
+    z = st.view("act0.blk0.z").view(T, ffn)
+    ref = torch.cat([dy[0].double().t() @ z[:, c:c + 2048].double() for c in range(0, ffn, 2048)], 1)
+    st.close()
+    # fp32 sums of T exact products of bf16 values: at most T 2^-24 of the sum of magnitudes, which for
+    # independent signs is about sqrt(T) times the result
+    tol = T ** 1.5 * 2.0 ** -24
+    assert _err(out[0], ref) < tol and _err(out[1], 2 * ref) < tol, (_err(out[0], ref), _err(out[1], 2 * ref), tol)
+
+
+@pytest.mark.parametrize("d,ffn,T", [(256, 4096, 300), (64, 2112, 17), (768, 3072, 999)], ids=["6-tiles", "1-tile", "48-tiles"])
+def test_split_activation_product(d, ffn, T):
+    # y = h + z Wd^T, K = ffn split over the idle blocks; one rounding to bf16 (at most 2^-9 per element)
+    import torch
+    st, x, dy = _stage(d, ffn, T)
+    y = torch.empty_like(x)
+    st.forward(0, 0, x_in=x, y_out=y)
+    torch.cuda.synchronize()
+    z, h = st.view("act0.blk0.z").double().view(T, ffn), st.view("act0.blk0.h").double().view(T, d)
+    ref = h + z @ st.view("w0.blk0.wdown").double().view(d, ffn).t()
+    e = _err(y[0], ref)
+    st.close()
+    assert e < 2.0 ** -8, e
+
+
+@pytest.mark.parametrize("d,ffn,T", [(64, 64, 31), (128, 512, 1000), (512, 2048, 2100)], ids=["32x32", "64x64", "128x128"])
+def test_fp32_tilings(d, ffn, T):
+    # gate | up = n2 Wgu^T (the SwiGLU in its epilogue); fp32 sums of K = d rounded products: at most
+    # 2 K 2^-24 of the sum of magnitudes, sqrt(K) times the result for independent signs
+    import torch
+    st, x, dy = _stage(d, ffn, T, bf16=False, heads=2, hd=32)
+    st.forward(0, 0, x_in=x, y_out=torch.empty_like(x))
+    torch.cuda.synchronize()
+    n2 = st.view("act0.blk0.n2").double().view(T, d)
+    g = n2 @ st.view("w0.blk0.wgate").double().view(ffn, d).t()
+    u = n2 @ st.view("w0.blk0.wup").double().view(ffn, d).t()
+    gu = st.view("act0.blk0.gu").view(T, 2 * ffn)
+    z = st.view("act0.blk0.z").view(T, ffn)
+    errs = (_err(gu[:, :ffn], g), _err(gu[:, ffn:], u), _err(z, torch.nn.functional.silu(g) * u))
+    st.close()
+    assert max(errs) < 2 * d ** 1.5 * 2.0 ** -24, errs
+
+
+@pytest.mark.parametrize("n", [1, 2, 65, 128, 129, 1000, 8191, 8192, 8193])
+def test_token_sort_lengths(n):
+    # a first stage without blocks: the embedding's gradient is the scatter of dy itself.  Ids and
+    # counts exact; each row the fp32 sum of its positions (50 ids, so up to n / 10 of them).
+    import torch
+    st, x, dy = _stage(64, 64, n, blocks=0, vocab=50, first=True)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(n)
+    tok = torch.randint(0, 50, (1, n), generator=gen, device="cuda:0", dtype=torch.int32)
+    st.forward(0, 0, tokens=tok, y_out=torch.empty_like(x))
+    st.backward(0, dy=dy)
+    torch.cuda.synchronize()
+    ids, counts = st.embed_indices(0)
+    rid, rc = torch.unique(tok.cpu(), return_counts=True)
+    assert list(ids) == rid.tolist() and list(counts) == rc.tolist()
+    ref = torch.zeros(50, 64, dtype=torch.float64, device="cuda:0").index_add_(0, tok[0].long(), dy[0].double())
+    e = _err(st.view("grad0.embed").view(50, 64), ref)
+    st.close()
+    assert e < n * 2.0 ** -24 + 1e-7, e

@@ -29,6 +29,11 @@ CASES = {
     "f32-vocab-1003": ("f32", "last", 1, 128, 2, 2, 64, 192, 1003, 61, 3),
     "f32-129-tokens": ("f32", "middle", 1, 192, 6, 2, 32, 320, 0, 43, 3),
     "f32-head-128": ("f32", "middle", 1, 128, 2, 1, 128, 64, 0, 67, 1),
+    # dk/dv items split 5 and 2 ways over their queries
+    "split-hd64": ("bf16", "middle", 1, 256, 4, 1, 64, 64, 0, 650, 1),
+    "split-hd128": ("bf16", "middle", 1, 256, 4, 2, 128, 64, 0, 515, 1),
+    # 11 norms: more than one batch of column sums
+    "f32-five-blocks": ("f32", "last", 5, 64, 2, 2, 32, 64, 97, 33, 2),
 }
 
 
