@@ -12,12 +12,13 @@
 //     4-byte read are 4 k-rows apart, which the pitch (8 mod 16) puts on the other 32 banks.
 // Bound: the matrix cores' 256 flop per cycle and CU (157 TFLOP/s on the chip) once the tiles fill
 // it; below that the serial chain of one tile, 64 cycles per 32 x 32 x 2 step.  Three tilings of one
-// block of 4 waves:
-//   128 x 128 (waves of 64 x 64), 64 x 64 (waves of 32 x 32), and 32 x 32 with the waves splitting
-//   every k-slice four ways (partial tiles summed in wave order through LDS).
+// block: 4 waves on 128 x 128 (waves of 64 x 64) or 64 x 64 (waves of 32 x 32), and 8 waves on 32 x 32
+// splitting every k-slice eight ways (partial tiles summed in wave order through LDS; with 4 waves the
+// same products took 10-15 % longer: [128, 128] over K 1024 13.0 -> 10.4 us, [1024, 512] over 4096 64.6 ->
+// 57.2 us).
 // Against the fp32 FMA tiling it replaced (64 x 64 tiles, 16-deep slices), a block's twelve products
-// alone: T = 1024, d 512, d_ffn 2048 2131 -> 409 us (63 TFLOP/s; up to 81 for one product), T = 128,
-// d 128, d_ffn 512 364 -> 75 us (4-9 us each, where a launch's latency is the bound).
+// alone: T = 1024, d 512, d_ffn 2048 2131 -> 401 us (64 TFLOP/s; up to 81 for one product), T = 128,
+// d 128, d_ffn 512 364 -> 66 us (4-10 us each, where a launch's latency is the bound).
 // Global loads are 16-byte vectors at any 4-byte alignment, element by element at the edges, into
 // registers one slice ahead; two LDS stages, one barrier per slice.
 #include "common.h"
@@ -32,17 +33,18 @@ struct Tiling {
   static constexpr int BM = BM_, BN = BN_, KW = KW_;  // KW: waves sharing a tile, each a part of every slice
   static constexpr int WM = KW > 1 ? BM : BM / 2, WN = KW > 1 ? BN : BN / 2;
   static constexpr int FM = WM / 32, FN = WN / 32;
-  static constexpr int BK = KW > 1 ? 64 : 32;  // slice depth
-  static constexpr int DW = BK / KW;           // depth of one wave's part
-  static_assert((BM / WM) * (BN / WN) * KW == 4 && DW % 8 == 0, "4 waves, whole 8-deep groups");
+  static constexpr int BK = KW > 1 ? 16 * KW : 32;  // slice depth
+  static constexpr int DW = BK / KW;                // depth of one wave's part
+  static constexpr int NW = (BM / WM) * (BN / WN) * KW, NT = 64 * NW;
+  static_assert(DW % 8 == 0 && (KW == 1 || 16 % KW == 0), "whole 8-deep groups, whole accumulators to each wave");
 };
 
-template <int ROWS, int BK, bool KMAJ>
+template <int ROWS, int BK, int NT, bool KMAJ>
 struct Operand {
   static constexpr int P = KMAJ ? BK + 4 : ROWS + 8;  // LDS row pitch
   static constexpr int ELEMS = KMAJ ? ROWS * P : BK * P;
-  static constexpr int PER = ROWS * BK / 4 / 256;  // chunks of 4 per thread and slice
-  static_assert(PER * 256 * 4 == ROWS * BK, "slice does not split evenly over the threads");
+  static constexpr int PER = ROWS * BK / 4 / NT;  // chunks of 4 per thread and slice
+  static_assert(PER * NT * 4 == ROWS * BK, "slice does not split evenly over the threads");
   f32x4 r[PER];
 
   // rowmap: tile row -> operand row (k-contiguous layout only)
@@ -51,7 +53,7 @@ struct Operand {
                                        F&& rowmap) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      const int c = threadIdx.x + p * 256;
+      const int c = threadIdx.x + p * NT;
       int row, k, left;  // the chunk's first element, and how many of its 4 elements exist
       if constexpr (KMAJ) {
         row = row0 + c / (BK / 4);
@@ -78,7 +80,7 @@ struct Operand {
   __device__ __forceinline__ void store(float* S) const {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      const int c = threadIdx.x + p * 256;
+      const int c = threadIdx.x + p * NT;
       const int o = KMAJ ? (c / (BK / 4)) * P + (c % (BK / 4)) * 4 : (c / (ROWS / 4)) * P + (c % (ROWS / 4)) * 4;
       *reinterpret_cast<f32x4*>(S + o) = r[p];
     }
@@ -145,10 +147,10 @@ __device__ __forceinline__ void put(const GemmArgs& g, int row, int n, float v) 
 }
 
 template <typename TL, bool AK, bool BKM>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs g) {
+__global__ void __launch_bounds__(TL::NT) gemm_f32_kernel(GemmArgs g) {
   constexpr int BM = TL::BM, BN = TL::BN, KW = TL::KW, FM = TL::FM, FN = TL::FN, BK = TL::BK;
-  using OA = Operand<BM, BK, AK>;
-  using OB = Operand<BN, BK, BKM>;
+  using OA = Operand<BM, BK, TL::NT, AK>;
+  using OB = Operand<BN, BK, TL::NT, BKM>;
   constexpr int STAGE = OA::ELEMS + OB::ELEMS;
   extern __shared__ __align__(16) float smem[];  // [2][A slice | B slice]
   if (g.batch > 1) {  // product blockIdx.z of a batch
@@ -211,19 +213,20 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs g) {
     __syncthreads();
   }
   if constexpr (KW > 1) {
-    // partial tiles to LDS as [wave][accumulator][lane]; wave w finishes rows 8 w .. 8 w + 7
+    // partial tiles to LDS as [wave][accumulator][lane]; wave w finishes accumulators EW w .. EW w + EW - 1
+    constexpr int EW = 16 / KW;
     float* red = smem;
     static_assert(KW * 16 * 64 <= 2 * STAGE, "partial tiles fit the stages");
 #pragma unroll
     for (int e = 0; e < 16; ++e) red[(wave * 16 + e) * 64 + lane] = acc[0][0][e];
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = 4 * wave + q;
+    for (int q = 0; q < EW; ++q) {
+      const int e = EW * wave + q;
       float v = red[e * 64 + lane];
 #pragma unroll
       for (int w = 1; w < KW; ++w) v += red[(w * 16 + e) * 64 + lane];
-      put(g, m0 + 8 * wave + 4 * (lane / 32) + q, n0 + lane % 32, v);
+      put(g, m0 + 8 * (e / 4) + 4 * (lane / 32) + e % 4, n0 + lane % 32, v);
     }
   } else {
 #pragma unroll
@@ -239,14 +242,14 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs g) {
 template <typename TL, bool AK, bool BKM>
 void launch_f32(const GemmArgs& g, hipStream_t st) {
   constexpr size_t lds = 2 * sizeof(float) *
-                         (Operand<TL::BM, TL::BK, AK>::ELEMS + Operand<TL::BN, TL::BK, BKM>::ELEMS);
+                         (Operand<TL::BM, TL::BK, TL::NT, AK>::ELEMS + Operand<TL::BN, TL::BK, TL::NT, BKM>::ELEMS);
   if constexpr (lds > 65536) {
     static const hipError_t attr = hipFuncSetAttribute((const void*)gemm_f32_kernel<TL, AK, BKM>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     (void)attr;
   }
   const unsigned nblk = (unsigned)(cdiv(g.M, TL::BM) * cdiv(g.N, TL::BN));
-  gemm_f32_kernel<TL, AK, BKM><<<dim3(nblk, 1, g.batch), 256, lds, st>>>(g);
+  gemm_f32_kernel<TL, AK, BKM><<<dim3(nblk, 1, g.batch), TL::NT, lds, st>>>(g);
 }
 
 template <typename TL>
@@ -261,12 +264,12 @@ void launch_layouts(const GemmArgs& g, hipStream_t st) {
 
 // Every fp32 product (plain, beta C, residual, batched, and epilogues 1, 2, 3 and 6; 2 and 3 with a
 // k-contiguous B).  The largest tiling that still gives each CU work: below 256 tiles of 64 x 64 the
-// 32 x 32 ones (T = 1024, N = 512, K = 4096: 63 us on 512 of them), from there 64 x 64 (N = 4096, K =
-// 512: 58 us against 69 on 32 x 32; 384-512 tiles are within 8 % either way), 128 x 128 once they fill
+// 32 x 32 ones (T = 1024, N = 512, K = 4096: 57 us on 512 of them), from there 64 x 64 (4096 x 512, K =
+// 1024: 54 us against 63 on 32 x 32; 384-512 tiles are within 10 % either way), 128 x 128 once they fill
 // two blocks per CU.
 void launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
   const int64_t t64 = cdiv(g.M, 64) * cdiv(g.N, 64) * g.batch, t128 = cdiv(g.M, 128) * cdiv(g.N, 128) * g.batch;
   if (t128 >= 512) launch_layouts<Tiling<128, 128, 1>>(g, st);
   else if (t64 >= 256) launch_layouts<Tiling<64, 64, 1>>(g, st);
-  else launch_layouts<Tiling<32, 32, 4>>(g, st);
+  else launch_layouts<Tiling<32, 32, 8>>(g, st);
 }
