@@ -15,9 +15,9 @@
 //   rebuilt from the S^T accumulators by one lane-pair exchange; lse = ln sum exp(S) is kept.
 // Backward (dS = P (dP - delta), delta = rowsum(dO O) with O in fp32, P recomputed from lse), two
 // kernels and no float atomics: dQ (waves own queries, K and V tiles streamed) and dK/dV (waves own keys, Q and
-// dO tiles of every query head of the key/value head streamed).  Tiles are double-buffered through
-// registers: the next tile is fetched while the current one feeds the MFMAs.  Outputs leave through
-// LDS as 16-byte rows.  Query blocks with the longest causal range are scheduled first.
+// dO tiles of every query head of the key/value head streamed; few key/value heads: each item's queries in
+// shares, added in order).  Streamed tiles go straight to a ring of LDS stages ahead of their use.  Outputs
+// leave through LDS as 16-byte rows.  Row blocks with the longest causal range are scheduled first.
 #include "common.h"
 #include "kernels.h"
 #include <algorithm>
