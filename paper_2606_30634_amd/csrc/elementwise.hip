@@ -509,7 +509,9 @@ __global__ void __launch_bounds__(64) radix_scatter(const int32_t* __restrict__ 
 // Few positions: the whole sort in one block, one launch in place of the nine above.  The keys are
 // token << 13 | position (30 bits), all different, so a bitonic network in LDS sorts them stably.  A
 // wave's 64 pairs span 128 consecutive keys while the partner distance is at most 64: those steps need no
-// barrier between the waves.  N: the power of two >= n, n <= SORT_ONE.
+// barrier between the waves, only the order of one lane's stores before another lane's loads (fences of
+// wavefront scope: a wave's LDS operations complete in issue order, so they cost no wait).  N: the power of
+// two >= n, n <= SORT_ONE.
 constexpr int SORT_ONE = 8192;
 __global__ void __launch_bounds__(1024) token_sort_one(const int32_t* __restrict__ tok, int n, int N, int vocab,
                                                        uint32_t* __restrict__ sorted_tok,
@@ -528,8 +530,13 @@ __global__ void __launch_bounds__(1024) token_sort_one(const int32_t* __restrict
         key[b] = up ? max(x, y) : min(x, y);
       }
       // the next step's pairs cross waves if this step's or its own distance exceeds 64
-      if (j > 64 || (j == 1 && k >= 128)) __syncthreads();
-      else __builtin_amdgcn_wave_barrier();
+      if (j > 64 || (j == 1 && k >= 128)) {
+        __syncthreads();
+      } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
     }
   }
   __syncthreads();
