@@ -33,6 +33,13 @@ __device__ __forceinline__ f32x16 mfma2(float a, float b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
+// Orders one lane's LDS accesses before another lane's of the same wave
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Four consecutive elements as fp32 (rows start on 4 elements: head_dim and every width are
 // multiples of 32)
 __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
@@ -55,6 +62,15 @@ struct RowFrag {
     const T* r = p + row * ld + 4 * (threadIdx.x % 64 / 32);
 #pragma unroll
     for (int q = 0; q < HD / 8; ++q) v[q] = ld4(r + 8 * q);
+  }
+  // whether every value of the wave's rows is finite (the sum stays 0 as long as they are)
+  __device__ __forceinline__ bool finite() const {
+    float z = 0.f;
+#pragma unroll
+    for (int q = 0; q < HD / 8; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) z = __builtin_fmaf(v[q][j], 0.f, z);
+    return __all(z == 0.f);
   }
 };
 // S (+)= A B^T over the head dimension: accumulator rows are A's rows, columns B's
@@ -88,6 +104,37 @@ __device__ __forceinline__ void cols_product(f32x16 (&acc)[HD / 32], const T* x,
 #pragma unroll
     for (int dt = 0; dt < HD / 32; ++dt) acc[dt] = mfma2(f[dt][e], w[e], acc[dt]);
 }
+
+// The same sum where some column does not see every tile row and a row holds an infinity or a NaN: its
+// weights there are 0, and 0 times such a value would be a NaN.  Row by row, each column the rows that
+// it sees (seen(r) for this lane's); tile: 32 x 32 floats of this wave's LDS.
+template <int HD, typename T, typename F>
+__device__ __forceinline__ void cols_product_seen(f32x16 (&acc)[HD / 32], const T* x, int row0, int ld,
+                                                  const f32x16& w, float* tile, F&& seen) {
+  const int lane = threadIdx.x % 64;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) tile[(8 * (e / 4) + 4 * (lane / 32) + e % 4) * TR + lane % 32] = w[e];
+  wave_fence();
+#pragma unroll
+  for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll 1
+    for (int r = 0; r < TR; ++r) {
+      if (!seen(r)) continue;
+      const float wr = tile[r * TR + lane % 32];
+      const T* xr = x + (int64_t)(row0 + r) * ld + 32 * dt + 4 * (lane / 32);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 v = ld4(xr + 8 * q);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[dt][4 * q + j] += wr * v[j];
+      }
+    }
+  wave_fence();
+}
+
+// LDS of one wave (floats): its partial sums, [dt][e][lane]
+template <int HD>
+constexpr int WAVE_LDS = (HD / 32) * 16 * 64;
 
 // Sum of the waves' accumulators over red ([wave][dt][e][lane]), in wave order.
 template <int HD>
@@ -155,13 +202,13 @@ __device__ __forceinline__ float pair_sum(float v) { return v + __shfl_xor(v, 32
 
 // One block per (32 queries, query head, sequence); longest causal ranges first.
 template <typename T, int HD>
-__global__ void __launch_bounds__(NW * 64) attn_fwd(AttnArgs a) {
-  __shared__ float red[NW * (HD / 32) * 16 * 64];
-  float (*stat)[NW][TR] = reinterpret_cast<float (*)[NW][TR]>(red);  // [2], before the partial sums
+__global__ void __launch_bounds__(NW * 64, HD == 128 ? 1 : HD == 64 ? 3 : 4) attn_fwd(AttnArgs a) {
+  __shared__ float red[NW * WAVE_LDS<HD>];
   const Geo g(a);
   const int b = blockIdx.z, h = blockIdx.y, kvh = h / g.group;
   const int q0 = (gridDim.x - 1 - blockIdx.x) * TR;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, q = q0 + lane % 32;
+  float* mine = red + wave * WAVE_LDS<HD>;  // this wave's part
   const T* qkv = (const T*)a.qkv + (int64_t)b * a.S * g.ld;
   const T* kp = qkv + g.koff + kvh * HD;
   const T* vp = qkv + g.voff + kvh * HD;
@@ -186,31 +233,39 @@ __global__ void __launch_bounds__(NW * 64) attn_fwd(AttnArgs a) {
       if (k0 + 8 * (e / 4) + 4 * (lane / 32) + e % 4 > q) s[e] = -INFINITY;
       mt = fmaxf(mt, s[e]);
     }
-    const float mn = fmaxf(m, pair_max(mt));  // finite: key k0 <= q0 is visible to every query
-    const float corr = expf(m - mn);          // 0 for the first tile
+    const float mn = fmaxf(m, pair_max(mt));
+    const float base = mn == -INFINITY ? 0.f : mn;  // no score above -inf yet: every weight 0
+    const float corr = expf(m - base);              // 0 for the first tile
     float rs = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      s[e] = expf(s[e] - mn);
+      s[e] = expf(s[e] - base);
       rs += s[e];
     }
     l = l * corr + pair_sum(rs);
     m = mn;
 #pragma unroll
     for (int dt = 0; dt < HD / 32; ++dt) o[dt] *= corr;
-    cols_product<HD>(o, vp, k0, a.S - 1, g.ld, s);
+    bool plain = true;
+    if (k0 == q0) {  // the tile whose keys some queries do not see
+      kf.load(vp, min(k0 + lane % 32, a.S - 1), g.ld);
+      plain = kf.finite();
+    }
+    if (plain) cols_product<HD>(o, vp, k0, a.S - 1, g.ld, s);
+    else cols_product_seen<HD>(o, vp, k0, g.ld, s, mine, [&](int r) { return k0 + r <= q && k0 + r < a.S; });
   }
   // the waves' statistics: o = sum_w e^(m_w - M) o_w / sum_w e^(m_w - M) l_w (wave 0 always has a tile)
   if (lane < TR) {
-    stat[0][wave][lane] = m;
-    stat[1][wave][lane] = l;
+    mine[lane] = m;
+    mine[TR + lane] = l;
   }
   __syncthreads();
   float M = -INFINITY, L = 0.f;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) M = fmaxf(M, stat[0][w][lane % 32]);
+  for (int w = 0; w < NW; ++w) M = fmaxf(M, red[w * WAVE_LDS<HD> + lane % 32]);
 #pragma unroll
-  for (int w = 0; w < NW; ++w) L += expf(stat[0][w][lane % 32] - M) * stat[1][w][lane % 32];
+  for (int w = 0; w < NW; ++w)
+    L += expf(red[w * WAVE_LDS<HD> + lane % 32] - M) * red[w * WAVE_LDS<HD> + TR + lane % 32];
   __syncthreads();
   put_partial<HD>(red, o, expf(m - M) / L);
   __syncthreads();
@@ -267,6 +322,7 @@ __device__ __forceinline__ void bwd_dq(const AttnArgs& a, int qb, int h, int b, 
     const int kr = min(k0 + lane % 32, a.S - 1);
     RowFrag<HD> f;
     f.load(kp, kr, g.ld);
+    const bool plain = k0 != q0 || f.finite();
     f32x16 s = rows_product<HD>(f, qf);
     f.load(vp, kr, g.ld);
     const f32x16 dp = rows_product<HD>(f, df);
@@ -275,7 +331,8 @@ __device__ __forceinline__ void bwd_dq(const AttnArgs& a, int qb, int h, int b, 
       const bool seen = k0 + 8 * (e / 4) + 4 * (lane / 32) + e % 4 <= q;
       s[e] = seen ? expf(s[e] - lse) * (dp[e] - dl) : 0.f;
     }
-    cols_product<HD>(dq, kp, k0, a.S - 1, g.ld, s);
+    if (plain) cols_product<HD>(dq, kp, k0, a.S - 1, g.ld, s);
+    else cols_product_seen<HD>(dq, kp, k0, g.ld, s, red + wave * WAVE_LDS<HD>, [&](int r) { return k0 + r <= q && k0 + r < a.S; });
   }
   put_partial<HD>(red, dq, 1.0f);
   __syncthreads();
@@ -308,19 +365,26 @@ __device__ __forceinline__ void bwd_dkv(const AttnArgs& a, int kb, int kvh, int 
     const T* dp_ = (const T*)a.dout + (int64_t)b * a.S * a.Hq * HD + h * HD;
     const int64_t sb = ((int64_t)b * a.Hq + h) * a.S;
     const int qr = min(q0 + lane % 32, a.S - 1);
+    const bool whole = q0 != k0 && q0 + TR <= a.S;  // every key sees every query of the tile
     RowFrag<HD> f;
     f.load(qp, qr, g.ld);
+    const bool plain_q = whole || f.finite();
     f32x16 p = rows_product<HD>(f, kf);  // rows: queries; column: this lane's key
     f.load(dp_, qr, a.Hq * HD);
+    const bool plain_d = whole || f.finite();
     f32x16 ds = rows_product<HD>(f, vf);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int q = q0 + 8 * (e / 4) + 4 * (lane / 32) + e % 4, qc = min(q, a.S - 1);
-      p[e] = q >= key && q < a.S ? expf(p[e] - a.lse[sb + qc]) : 0.f;
-      ds[e] = p[e] * (ds[e] - a.delta[sb + qc]);
+      const bool sees = q >= key && q < a.S;
+      p[e] = sees ? expf(p[e] - a.lse[sb + qc]) : 0.f;
+      ds[e] = sees ? p[e] * (ds[e] - a.delta[sb + qc]) : 0.f;
     }
-    cols_product<HD>(dv, dp_, q0, a.S - 1, a.Hq * HD, p);
-    cols_product<HD>(dk, qp, q0, a.S - 1, g.ld, ds);
+    auto seen = [&](int r) { return q0 + r >= key && q0 + r < a.S; };
+    if (plain_d) cols_product<HD>(dv, dp_, q0, a.S - 1, a.Hq * HD, p);
+    else cols_product_seen<HD>(dv, dp_, q0, a.Hq * HD, p, red + wave * WAVE_LDS<HD>, seen);
+    if (plain_q) cols_product<HD>(dk, qp, q0, a.S - 1, g.ld, ds);
+    else cols_product_seen<HD>(dk, qp, q0, g.ld, ds, red + wave * WAVE_LDS<HD>, seen);
   }
   T* out = (T*)a.dqkv + (int64_t)b * a.S * g.ld;
   put_partial<HD>(red, dk, 1.0f);
@@ -335,8 +399,8 @@ __device__ __forceinline__ void bwd_dkv(const AttnArgs& a, int kb, int kvh, int 
 // dk/dv blocks (first, low keys see the most queries) and dq blocks (longest ranges first) in one
 // launch: independent given delta, and together they fill more of the chip.
 template <typename T, int HD>
-__global__ void __launch_bounds__(NW * 64) attn_bwd(AttnArgs a) {
-  __shared__ float red[NW * (HD / 32) * 16 * 64];
+__global__ void __launch_bounds__(NW * 64, HD == 128 ? 1 : 2) attn_bwd(AttnArgs a) {
+  __shared__ float red[NW * WAVE_LDS<HD>];
   const int h = blockIdx.y, b = blockIdx.z;
   if (h < a.Hkv) bwd_dkv<T, HD>(a, blockIdx.x, h, b, red);
   else bwd_dq<T, HD>(a, gridDim.x - 1 - blockIdx.x, h - a.Hkv, b, red);
