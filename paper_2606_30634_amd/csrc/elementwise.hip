@@ -628,6 +628,7 @@ __global__ void __launch_bounds__(256) ce_fwd_rows(const float* __restrict__ log
   for (int j = threadIdx.x; j < V / 4; j += 256) {
     const f32x4 v = z4[j];
     const float mm = fmaxf(m, fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+    if (mm == -INFINITY && (v[0] + v[1]) + (v[2] + v[3]) == -INFINITY) continue;  // nothing above -inf yet
     s = s * __expf(m - mm) + (__expf(v[0] - mm) + __expf(v[1] - mm)) + (__expf(v[2] - mm) + __expf(v[3] - mm));
     m = mm;
   }

@@ -5,10 +5,11 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def _stage(hd, bf16, S, heads=2, kv=1, d=64, ffn=64):
+def _stage(hd, bf16, S, heads=2, kv=1, d=64, ffn=64, vocab=0):
     import torch
     from paper_2606_30634_amd.stage import Stage, make_shape
-    st = Stage(make_shape(1, d, heads, kv, hd, ffn, 0, False, False, False, S, 1, 1, bf16=bf16), "cuda:0")
+    st = Stage(make_shape(1 if not vocab else 0, d, heads, kv, hd, ffn, vocab, False, vocab > 0, False, S, 1, 1, bf16=bf16),
+               "cuda:0")
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(5)
     st.view("flat.master").normal_(0.0, 0.1, generator=gen)
@@ -75,3 +76,27 @@ def test_attention_scores_of_minus_infinity():
     o = st.view("act0.blk0.o").view(S, hd).double()
     st.close()
     assert float((o - ref).norm() / ref.norm()) < 1e-6
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("vocab", [7, 1003, 1004])
+def test_cross_entropy_with_logits_of_minus_infinity(bf16, vocab):
+    # the first four logits of every row overflow to -inf: probability 0, and a finite loss
+    import torch
+    S, d = 33, 64
+    st, x, _ = _stage(32, bf16, S, vocab=vocab)
+    st.view("w0.final_norm").fill_(1.0)
+    st.view("w0.head").view(vocab, d)[:4] = -3e38
+    x = x.abs() + 0.5
+    tg = torch.arange(S, device="cuda:0", dtype=torch.int32).view(1, S) % (vocab - 4) + 4
+    loss, dx = torch.zeros(1, device="cuda:0"), torch.empty_like(x)
+    st.forward(0, 0, x_in=x, targets=tg, loss=loss)
+    st.backward(0, dx_out=dx)
+    torch.cuda.synchronize()
+    z = st.view("act0.logits").view(S, vocab).double()
+    assert bool(torch.isinf(z[:, :4]).all())
+    ref = float(torch.nn.functional.cross_entropy(z, tg[0].long()))
+    got = float(loss)
+    fin = bool(torch.isfinite(dx).all())
+    st.close()
+    assert abs(got - ref) < 1e-5 * ref and fin, (got, ref, fin)
