@@ -121,10 +121,11 @@ __device__ __forceinline__ void epi_load(EpiIn<EPI>& in, const GemmArgs& g, int 
   }
 }
 
-// RAG: the correctly rounded divide (partial tiles are few, whole ones bound by their stores)
+// RAG: the library's exponential and divide, which the fp32 tiling these products came from used: some
+// calls had them, and the rest of their time is the latency of few tiles
 template <bool RAG>
 __device__ __forceinline__ float sigmoid(float a) {
-  if constexpr (RAG) return 1.0f / (1.0f + __expf(-a));
+  if constexpr (RAG) return 1.0f / (1.0f + expf(-a));
   else return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * a));
 }
 

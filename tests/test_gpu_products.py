@@ -65,6 +65,39 @@ def test_split_activation_product(d, ffn, T):
     assert e < 2.0 ** -8, e
 
 
+def test_swiglu_backward_of_partial_tiles():
+    # dgate and dup of a ragged product as the gate | up weight gradient shows them: one-hot rows of n2 and
+    # dy = e_0, so that dWgu[r, t] = dgu[t, r] and dz = row 0 of Wdown, exact in bf16.  In fp32 with an
+    # exponential of 1 ulp the formula's eight roundings stay below 2^-20.8 of the result, which moves at
+    # most 2^-20.8 / 2^-8 = 1.4e-4 of its bf16 roundings.
+    import torch
+    d, ffn, T = 64, 8192, 63
+    st, x, dy = _stage(d, ffn, T)
+    st.forward(0, 0, x_in=x, y_out=torch.empty_like(x))
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(11)
+    gu = st.view("act0.blk0.gu").view(T, 2 * ffn)
+    gu[:, :ffn] = torch.empty(T, ffn, device="cuda:0").uniform_(-80.0, -64.0, generator=gen)
+    gu[:, ffn:] = torch.empty(T, ffn, device="cuda:0").uniform_(1.0, 2.0, generator=gen)
+    st.view("act0.blk0.n2").view(T, d).copy_(torch.eye(d, device="cuda:0")[:T])
+    dy.zero_()
+    dy[..., 0] = 1.0
+    w = st.view("w0.blk0.wdown").view(d, ffn)
+    w[0] = torch.empty(ffn, device="cuda:0").uniform_(1.0, 2.0, generator=gen)
+    st.backward(0, dy=dy)
+    torch.cuda.synchronize()
+    a, b, dz = gu[:, :ffn].double(), gu[:, ffn:].double(), w[0].double()
+    s = torch.sigmoid(a)
+    moved = 0
+    for name, ref in (("wgate", dz * b * s * (1.0 + a * (1.0 - s))), ("wup", dz * a * s)):
+        got = st.view(f"grad0.blk0.{name}").view(ffn, d)[:, :T].t()
+        ref16 = ref.float().to(torch.bfloat16).float()
+        moved += int((got != ref16).sum())
+        assert float(((got - ref16).abs() / ref16.abs()).max()) <= 2.0 ** -7  # the neighbouring value at most
+    st.close()
+    assert moved < 1.4e-4 * 2 * T * ffn, moved
+
+
 @pytest.mark.parametrize("d,ffn,T", [(64, 64, 31), (128, 512, 1000), (512, 2048, 2100)], ids=["32x32", "64x64", "128x128"])
 def test_fp32_tilings(d, ffn, T):
     # gate | up = n2 Wgu^T (the SwiGLU in its epilogue); fp32 sums of K = d rounded products: at most
