@@ -971,6 +971,7 @@ __device__ __forceinline__ void bwd_dkv128_block(const AttnArgs& a, int kbk, int
       next_tile();  // into the stage before prev
       step(t0, yes, yes, yes, yes, cur, prev, qp + 32, prev);
       step(t1, yes, yes, yes, yes, cur, cur, qc, prev);
+      acc_settled(dk, dv);  // register copies the compiler may place at the loop's end
     }
     acc_settled(dk, dv);
     step(t0, no, yes, yes, no, cur, cur, qc + 32, cur);
