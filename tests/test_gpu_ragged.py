@@ -32,6 +32,11 @@ CASES = {
     # dk/dv items split 5 and 2 ways over their queries
     "split-hd64": ("bf16", "middle", 1, 256, 4, 1, 64, 64, 0, 650, 1),
     "split-hd128": ("bf16", "middle", 1, 256, 4, 2, 128, 64, 0, 515, 1),
+    # the same over several sequences (the batch term of the partial sums' layout)
+    "split-hd64-3-sequences": ("bf16", "middle", 1, 256, 4, 1, 64, 64, 0, 650, 3),
+    "split-hd128-2-sequences": ("bf16", "middle", 1, 256, 4, 2, 128, 64, 0, 515, 2),
+    # the last key block has one tile of queries for two shares: one share adds nothing
+    "split-empty-share": ("bf16", "middle", 1, 128, 1, 1, 128, 64, 0, 1025, 1),
     # 11 norms: more than one batch of column sums
     "f32-five-blocks": ("f32", "last", 5, 64, 2, 2, 32, 64, 97, 33, 2),
 }
