@@ -814,11 +814,16 @@ bool use_wide(const GemmArgs& g) {
 
 // Splits of a deep bf16-output product of few tiles (plain or with a residual): up to one round of the
 // 512 blocks the chip holds, at least 512 of K each.  M 999, N 768: K 32001 379 -> 92 us, K 6144
-// 67 -> 27 us, the sum over the splits included.
+// 67 -> 27 us, the sum over the splits included.  That sum costs 8-14 us with the partial tiles' traffic,
+// and the more tiles there are, the less a split gains: K from 256 + 15 tiles on.  Unsplit against split,
+// NT and NN: 96 tiles K 2048 23 : 19 us; 128 tiles K 2048 21 : 22.5, K 2816 31 : 26; 160 tiles K 2048
+// 24 : 26.5, K 2816 31 : 30; 192 tiles K 2048 23.5 : 25.5, K 2816 31 : 30, K 4096 42 : 37; 256 tiles K 2048
+// 26 : 31, K 2816 34 : 36.5, K 4096 47 : 44.5, K 5632 62 : 56.
 int activation_splits(const GemmArgs& g) {
   if (g.out_f32 || !g.ws || g.epi != 0 || g.batch > 1 || g.sym || g.ldc != g.N || !g.a_kmajor || g.K < 2048) return 1;
   if ((uintptr_t)g.resid % 16) return 1;
   const int64_t tiles = cdiv(g.M, 128) * cdiv(g.N, 128), slices = cdiv(g.K, BKT), mn = (int64_t)g.M * g.N;
+  if (g.K < 256 + 15 * tiles) return 1;
   int s = (int)std::min<int64_t>(8, 512 / tiles);
   while (s > 1 && (s * mn > g.ws_elems || g.K / s < 512 || (s - 1) * cdiv(slices, s) >= slices)) --s;
   return s;
