@@ -833,13 +833,17 @@ int activation_splits(const GemmArgs& g) {
 // round would take a round to themselves at a half or less of the blocks, so they are split over K as far
 // as a round holds them.  K 8192: 4096 x 14336, 768 + 128 tiles, 824 -> 777 us; 49152 x 768, 512 + 64, 624 ->
 // 576 us.  (128 x 128 tiles gain nothing: 2048 x 6144, 512 + 256 tiles, 195 -> 202 us.)
+// s splits save 1 - 1/s of the tail's round, in proportion to K, and write and sum s tail partial tiles:
+// they break even at K (s - 1) = 8 s^2 tail.  Whole against split: tail 128, s 2: K 2048 107 : 121 us, 3072
+// 151 : 157, 4096 195 : 193, 6144 279 : 265; tail 96, s 2: K 2048 104 : 110, 3072 147 : 145, 4096 189 : 178;
+// tail 64, s 4: K 2048 104.5 : 109, 3072 147 : 140; tail 14, s 4: K 2048 101 : 83.
 bool launch_tail_split(const GemmArgs& g, hipStream_t st) {
   constexpr int B = 256, WM = 64, WN = 128, slots = 256;
   const int tiles = (g.M / B) * (g.N / B), tail = tiles % slots, slices = g.K / BKT;
   if (!g.out_f32 || g.ksplit > 1 || !g.ws || tiles < slots || tail == 0 || tail > slots / 2) return false;
   int s = std::min(8, slots / tail);
   while (s > 1 && (slices % s || g.K / s < 512 || (int64_t)s * tail * B * B > g.ws_elems)) --s;
-  if (s < 2) return false;
+  if (s < 2 || (int64_t)g.K * (s - 1) < (int64_t)8 * s * s * tail) return false;
   GemmArgs p = g;
   p.tile_n = tiles - tail;
   if (!launch_dma<B, B, WM, WN, false>(p, st)) return false;

@@ -44,9 +44,10 @@ def _sum_tol(K):
 @pytest.mark.parametrize("d,ffn,T", [
     (768, 3072, 2048),    # 144 tiles of 128 x 128 in 4 splits just past a round: 128 x 192 tiles
     (2048, 5632, 2048),   # 176 tiles of 256 x 256: one round of them
-    (4096, 14336, 2048),  # 896 tiles of 256 x 256: the last 128 split over K
-    (768, 3072, 2056),    # the same widths over a ragged K
-], ids=["wide", "one-round", "tail", "ragged"])
+    (4096, 14336, 2048),  # 896 tiles of 256 x 256, 3.5 rounds: not deep enough to split the last 128
+    (2560, 6912, 2048),   # 270 tiles of 256 x 256: the last 14 split over K
+    (768, 3072, 2056),    # the widths of the first over a ragged K
+], ids=["wide", "one-round", "half-round", "tail", "ragged"])
 def test_weight_gradient_tiles(d, ffn, T):
     import torch
     st, x, dy = _stage(d, ffn, T)
