@@ -126,14 +126,14 @@ void launch_axpby(bool bf, void* y, const void* x, float alpha, float beta, int 
 void launch_gemm(bool bf, const GemmArgs& g, hipStream_t st) {
   if (g.M == 0 || g.N == 0) return;
   if (bf && gemm_mfma_try(g, st)) return;
-  if (!bf && g.epi != 4) {
-    launch_gemm_f32(g, st);
-    return;
-  }
   if (g.epi == GEMM_EPI_AXPBY_DUP || g.epi == GEMM_EPI_NS_SPLIT) {
     // only the batched direct-to-LDS kernels implement these; callers check gemm_batched_tiles()
     fprintf(stderr, "launch_gemm: epilogue %d needs whole tiles and bf16 operands\n", g.epi);
     abort();
+  }
+  if (!bf && g.epi != 4) {
+    launch_gemm_f32(g, st);
+    return;
   }
   if (g.batch > 1 || g.epi == GEMM_EPI_AXPBY) {
     // one product at a time, then the AXPBY pass

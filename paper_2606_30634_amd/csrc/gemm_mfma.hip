@@ -864,7 +864,7 @@ bool dma_operands(const GemmArgs& g) {
   if (!g.a_padded && (g.a_kmajor ? g.K : g.M) % 8) return false;
   if ((g.b_kmajor ? g.K : g.N) % 8) return false;
   if (!g.out_f32 && (g.N % 8 || g.ldc % 8)) return false;
-  return 256 * (int64_t)std::max(g.lda, g.ldb) + (int64_t)g.glu * g.ldb < ((int64_t)1 << 30);
+  return 256 * (int64_t)std::max(g.lda, g.ldb) < ((int64_t)1 << 30);
 }
 
 }  // namespace
@@ -908,9 +908,10 @@ bool gemm_mfma_try(const GemmArgs& g0, hipStream_t st) {
   }
   if (g.epi == 3) {
     // the SwiGLU forward rides in the epilogue (the B loader gathers gate and up rows) when the
-    // panels are whole; any other shape runs the product, then the SwiGLU kernel
+    // panels are whole and the up rows within a tile offset of the gate rows; any other shape runs the
+    // product, then the SwiGLU kernel
     const bool fused = !g.out_f32 && g.b_kmajor && g.N == 2 * g.glu && g.glu % 64 == 0 && g.ld_out2 % 8 == 0 &&
-                       (uintptr_t)g.out2 % 16 == 0;
+                       (uintptr_t)g.out2 % 16 == 0 && (256 + (int64_t)g.glu) * g.ldb < ((int64_t)1 << 30);
     if (!fused) {
       GemmArgs p = g;
       p.epi = 0;

@@ -116,6 +116,24 @@ def test_swiglu_backward_of_partial_tiles():
     assert moved < 1.4e-4 * 2 * T * ffn, moved
 
 
+def test_gate_and_up_rows_past_a_tile_offset():
+    # d_ffn x d_model above 2^30: the up rows are out of reach of the gate rows' tile offsets, so the
+    # product runs first and the SwiGLU after it
+    import torch
+    d, ffn, T = 4096, 262208, 128
+    st, x, dy = _stage(d, ffn, T)
+    st.forward(0, 0, x_in=x, y_out=torch.empty_like(x))
+    torch.cuda.synchronize()
+    n2 = st.view("act0.blk0.n2").view(T, d).double()
+    cols = torch.tensor([0, 1, 63, 64, 131071, ffn - 65, ffn - 1], device="cuda:0")
+    g = n2 @ st.view("w0.blk0.wgate").view(ffn, d)[cols].double().t()
+    u = n2 @ st.view("w0.blk0.wup").view(ffn, d)[cols].double().t()
+    gu, z = st.view("act0.blk0.gu").view(T, 2 * ffn), st.view("act0.blk0.z").view(T, ffn)
+    errs = (_err(gu[:, cols], g), _err(gu[:, ffn + cols], u), _err(z[:, cols], torch.nn.functional.silu(g) * u))
+    st.close()
+    assert max(errs) < 2.0 ** -8, errs
+
+
 @pytest.mark.parametrize("d,ffn,T", [(64, 64, 31), (128, 512, 1000), (512, 2048, 2100)], ids=["32x32", "64x64", "128x128"])
 def test_fp32_tilings(d, ffn, T):
     # gate | up = n2 Wgu^T (the SwiGLU in its epilogue): fp32 sums of K = d products; z from both, with
