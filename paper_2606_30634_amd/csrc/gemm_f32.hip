@@ -14,7 +14,7 @@
 // it; below that the serial chain of one tile, 64 cycles per 32 x 32 x 2 step.  Three tilings of one
 // block: 4 waves on 128 x 128 (waves of 64 x 64) or 64 x 64 (waves of 32 x 32), and 8 waves on 32 x 32
 // splitting every k-slice eight ways (partial tiles summed in wave order through LDS; with 4 waves the
-// same products took 10-15 % longer: [128, 128] over K 1024 13.0 -> 10.4 us, [1024, 512] over 4096 64.6 ->
+// same products took 13-25 % longer: [128, 128] over K 1024 13.0 -> 10.4 us, [1024, 512] over 4096 64.6 ->
 // 57.2 us).
 // Against the fp32 FMA tiling it replaced (64 x 64 tiles, 16-deep slices), a block's twelve products
 // alone: T = 1024, d 512, d_ffn 2048 2131 -> 401 us (64 TFLOP/s; up to 81 for one product), T = 128,
