@@ -8,8 +8,9 @@
 //   - an operand whose global layout is row-contiguous (W in dy W, both operands of dy^T x) is
 //     staged as it sits in memory ([k][row], 16-byte chunks) and its fragments are read with
 //     gfx950's transposing LDS read ds_read_b64_tr_b16.
-// Block tiles are 128 x 128 (4 waves of 64 x 64) or 256 x 256 (8 waves of 64 x 128) with 64-deep
-// k-slices that go straight from global memory to LDS.  Inside a k-slice the fragments of the next
+// Block tiles are 128 x 128 (4 waves of 64 x 64), 256 x 256 (8 waves of 64 x 128) or, for weight
+// gradients, 128 x 192 (4 waves of 64 x 96), with 64-deep k-slices that go straight from global memory
+// to LDS.  Inside a k-slice the fragments of the next
 // 16-deep step are read from LDS while the MFMAs of the current one run.  The epilogue stages each
 // wave's tile through LDS and writes 16-byte rows.  Block order is remapped so that consecutive
 // tiles of one output row band land on one XCD (one L2).  Deterministic split-K for underfilled
@@ -793,8 +794,8 @@ bool launch_dma(const GemmArgs& g, hipStream_t st) {
 // rounds, 109 -> 91 us; N 49152: 700 -> 646; N 3072, 1.5 rounds: 69 -> 80 us), from K = 1536 on anyway.
 bool use_big(const GemmArgs& g) {
   const int64_t t256 = cdiv(g.M, 256) * cdiv(g.N, 256), rounds = cdiv(t256, 256);
-  // fp32 products of 129-255 tiles: one round, where 128 x 128 tiles take two (K 8192, 2048 x 6144: 201 ->
-  // 176 us)
+  // fp32 products of 129-255 tiles: one round, where 128 x 128 tiles take two (K 8192: 2048 x 6144 201 -> 176
+  // us, 2048 x 5632 182 -> 163; where one round of 128 x 192 tiles holds it, that measures 166 for the first)
   if (g.out_f32 && g.K >= 2048 && g.M % 256 == 0 && g.N % 256 == 0 && t256 > 128 && t256 < 256) return true;
   return (g.K >= 768 && t256 >= 512 && 10 * t256 >= 9 * 256 * rounds) ||
          (g.K >= 1536 && (t256 >= 512 || (t256 >= 256 && g.K >= 2048)));
@@ -829,7 +830,7 @@ int activation_splits(const GemmArgs& g) {
   return s;
 }
 
-// fp32 products of whole 256 x 256 tiles over more than two rounds of 256: the tiles past the last full
+// fp32 products of whole 256 x 256 tiles over more than one round of 256: the tiles past the last full
 // round would take a round to themselves at a half or less of the blocks, so they are split over K as far
 // as a round holds them.  K 8192: 4096 x 14336, 768 + 128 tiles, 824 -> 777 us; 49152 x 768, 512 + 64, 624 ->
 // 576 us.  (128 x 128 tiles gain nothing: 2048 x 6144, 512 + 256 tiles, 195 -> 202 us.)
