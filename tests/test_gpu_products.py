@@ -153,7 +153,7 @@ def test_fp32_tilings(d, ffn, T):
     assert max(errs[:2]) < tol and errs[2] < 2 * tol + 6 * 2.0 ** -24, (errs, tol)
 
 
-@pytest.mark.parametrize("n", [1, 2, 65, 128, 129, 1000, 8191, 8192, 8193])
+@pytest.mark.parametrize("n", [1, 2, 65, 128, 129, 1000, 4095, 4096, 4097, 8191, 8192, 8193])
 def test_token_sort_lengths(n):
     # a first stage without blocks: the embedding's gradient is the scatter of dy itself.  Ids and
     # counts exact; each row the fp32 sum of its positions (50 ids, so up to n / 10 of them).
