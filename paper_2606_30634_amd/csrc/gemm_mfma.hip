@@ -788,6 +788,11 @@ bool launch_dma(const GemmArgs& g, hipStream_t st) {
                    : launch_dma_cfg<BM, BN, WM, WN, bf16, BKT, 2, RAG>(g, st);
 }
 
+// Whether the chip holds all blocks of `tiles` 128 x 128 tiles in s splits at once (two per CU; the launcher
+// gives every split a multiple of 8 of them).  One block more takes a second round: K 4104, 2304 x 768, 108
+// tiles, 5 splits 39 us, 4 splits 28; K 8200, 2688 x 512, 84 tiles, 6 splits (80 blocks each) 53, 5 splits 36.
+bool one_round(int64_t tiles, int s) { return s == 1 || tiles <= 512 / s / 8 * 8; }
+
 // Tile choice: 256 x 256 (8 waves of 64 x 128, 64-deep slices in 2 stages, one block per CU) when the
 // product has enough of them and is deep enough for the larger tile to pay, else 128 x 128 (two blocks
 // per CU).  From K = 768 it pays where its rounds of 256 tiles are nearly full (M 8192, K 768, N 6144: 3
@@ -826,7 +831,8 @@ int activation_splits(const GemmArgs& g) {
   const int64_t tiles = cdiv(g.M, 128) * cdiv(g.N, 128), slices = cdiv(g.K, BKT), mn = (int64_t)g.M * g.N;
   if (g.K < 256 + 15 * tiles) return 1;
   int s = (int)std::min<int64_t>(8, 512 / tiles);
-  while (s > 1 && (s * mn > g.ws_elems || g.K / s < 512 || (s - 1) * cdiv(slices, s) >= slices)) --s;
+  while (s > 1 && (s * mn > g.ws_elems || g.K / s < 512 || !one_round(tiles, s) || (s - 1) * cdiv(slices, s) >= slices))
+    --s;
   return s;
 }
 
@@ -843,7 +849,7 @@ bool launch_tail_split(const GemmArgs& g, hipStream_t st) {
   const int tiles = (g.M / B) * (g.N / B), tail = tiles % slots, slices = g.K / BKT;
   if (!g.out_f32 || g.ksplit > 1 || !g.ws || tiles < slots || tail == 0 || tail > slots / 2) return false;
   int s = std::min(8, slots / tail);
-  while (s > 1 && (slices % s || g.K / s < 512 || (int64_t)s * tail * B * B > g.ws_elems)) --s;
+  while (s > 1 && (slices % s || g.K / s < 512 || tail > slots / s / 8 * 8 || (int64_t)s * tail * B * B > g.ws_elems)) --s;
   if (s < 2 || (int64_t)g.K * (s - 1) < (int64_t)8 * s * s * tail) return false;
   GemmArgs p = g;
   p.tile_n = tiles - tail;
@@ -936,10 +942,10 @@ bool gemm_mfma_try(const GemmArgs& g0, hipStream_t st) {
   const int64_t slices = cdiv(g.K, BKT);
   if (g.out_f32 && g.ws && g.ldc == g.N && tiles < 512 && g.K >= 2048) {
     // deterministic split-K for underfilled fp32-output products: whole slices per split, equal
-    // splits where K is a whole number of slices, none empty otherwise
+    // splits where K is a whole number of slices, otherwise none empty and all in one round
     int s = big && tiles < 256 ? 1 : (int)std::min<int64_t>(8, cdiv(512, tiles));
     while (s > 1 && (s * mn > g.ws_elems || g.K / s < 512 ||
-                     (g.K % BKT == 0 ? slices % s != 0 : (s - 1) * cdiv(slices, s) >= slices)))
+                     (g.K % BKT == 0 ? slices % s != 0 : !one_round(tiles, s) || (s - 1) * cdiv(slices, s) >= slices)))
       --s;
     g.ksplit = s;
   }
