@@ -794,16 +794,31 @@ bool launch_dma(const GemmArgs& g, hipStream_t st) {
 bool one_round(int64_t tiles, int s) { return s == 1 || tiles <= 512 / s / 8 * 8; }
 
 // Tile choice: 256 x 256 (8 waves of 64 x 128, 64-deep slices in 2 stages, one block per CU) when the
-// product has enough of them and is deep enough for the larger tile to pay, else 128 x 128 (two blocks
-// per CU).  From K = 768 it pays where its rounds of 256 tiles are nearly full (M 8192, K 768, N 6144: 3
-// rounds, 109 -> 91 us; N 49152: 700 -> 646; N 3072, 1.5 rounds: 69 -> 80 us), from K = 1536 on anyway.
+// product has enough of them, is deep enough and fills their rounds of 256, else 128 x 128 (two blocks per
+// CU, rounds of 512).  Measured 128 x 128 against 256 x 256:
+//   - from K = 1536 on enough tiles decide;
+//   - from K = 768 to there C has to fill 92 % of the rounds (M 8192, K 768, N 6144, 3 rounds: 92 : 81 us; M
+//     20480, N 5632, K 1024, 6.9 of 7: 257 : 233; M 8192 there, 2.75 of 3: 99.6 : 102.7); 97 %, whole columns
+//     and K 1280 for the SwiGLU backward, whose two outputs and reads one block per CU hides less (M 16384:
+//     N 3072, K 768 121 : 126; N 2816, K 1024 123 : 138; N 5120, K 1280 279 : 265); 85 % where RoPE or delta
+//     of 128-wide heads ride in the epilogue of the larger tile only (M 16384, N 2688, K 896: 125 : 97);
+//   - a C of whole 128 x 128 but not 256 x 256 tiles takes the larger ones, partial at its edge, when they
+//     need half the rounds (0.6 of them in fp32, or with those heads) and lie to a tenth outside C at most:
+//     K 5120, 8192 x 1920, 1 : 2 rounds 148 : 142; K 5888, 8192 x 2176, 2 : 3 rounds 217 : 280; K 2432, 32768 x
+//     896, an eighth outside, 137 : 149; fp32 over K 4096: 17408 x 3200, 4 : 7 rounds, 465 : 412, 10240 x 1920,
+//     2 : 3, 154 : 194.
 bool use_big(const GemmArgs& g) {
-  const int64_t t256 = cdiv(g.M, 256) * cdiv(g.N, 256), rounds = cdiv(t256, 256);
+  const int64_t t256 = cdiv(g.M, 256) * cdiv(g.N, 256), rounds = cdiv(t256, 256), mn = (int64_t)g.M * g.N;
   // fp32 products of 129-255 tiles: one round, where 128 x 128 tiles take two (K 8192: 2048 x 6144 201 -> 176
   // us, 2048 x 5632 182 -> 163; where one round of 128 x 192 tiles holds it, that measures 166 for the first)
   if (g.out_f32 && g.K >= 2048 && g.M % 256 == 0 && g.N % 256 == 0 && t256 > 128 && t256 < 256) return true;
-  return (g.K >= 768 && t256 >= 512 && 10 * t256 >= 9 * 256 * rounds) ||
-         (g.K >= 1536 && (t256 >= 512 || (t256 >= 256 && g.K >= 2048)));
+  const bool heads = (g.epi == 2 && g.rope_hd == 128) || (g.epi == 4 && g.delta_hd == 128);
+  if (g.M % 128 == 0 && g.N % 128 == 0 && g.K % BKT == 0 && (g.M % 256 || g.N % 256) &&
+      (10 * rounds > (g.out_f32 || heads ? 6 : 5) * cdiv(mn, 512 * 128 * 128) || 10 * 65536 * t256 > 11 * mn))
+    return false;
+  if (g.K >= 1536) return t256 >= 512 || (t256 >= 256 && g.K >= 2048);
+  if (g.K < 768 || t256 < 512 || (g.epi == 1 && (g.K < 1280 || g.N % 256))) return false;
+  return 100 * mn >= (g.epi == 1 ? 97 : heads ? 85 : 92) * 65536 * 256 * rounds;
 }
 
 // Weight-gradient products (fp32, row-contiguous operands) whose 128 x 128 blocks just miss a round of
@@ -821,15 +836,15 @@ bool use_wide(const GemmArgs& g) {
 // Splits of a deep bf16-output product of few tiles (plain or with a residual): up to one round of the
 // 512 blocks the chip holds, at least 512 of K each.  M 999, N 768: K 32001 379 -> 92 us, K 6144
 // 67 -> 27 us, the sum over the splits included.  That sum costs 8-14 us with the partial tiles' traffic,
-// and the more tiles there are, the less a split gains: K from 256 + 15 tiles on.  Unsplit against split,
+// and the more tiles there are, the less a split gains: K above 640 + 11 tiles.  Unsplit against split,
 // NT and NN: 96 tiles K 2048 23 : 19 us; 128 tiles K 2048 21 : 22.5, K 2816 31 : 26; 160 tiles K 2048
-// 24 : 26.5, K 2816 31 : 30; 192 tiles K 2048 23.5 : 25.5, K 2816 31 : 30, K 4096 42 : 37; 256 tiles K 2048
+// 24 : 26.5, K 2816 31 : 30; 192 tiles K 2048 23.5 : 25.5, K 2816 31 : 29.5, K 4096 42 : 37; 256 tiles K 2048
 // 26 : 31, K 2816 34 : 36.5, K 4096 47 : 44.5, K 5632 62 : 56.
 int activation_splits(const GemmArgs& g) {
   if (g.out_f32 || !g.ws || g.epi != 0 || g.batch > 1 || g.sym || g.ldc != g.N || !g.a_kmajor || g.K < 2048) return 1;
   if ((uintptr_t)g.resid % 16) return 1;
   const int64_t tiles = cdiv(g.M, 128) * cdiv(g.N, 128), slices = cdiv(g.K, BKT), mn = (int64_t)g.M * g.N;
-  if (g.K < 256 + 15 * tiles) return 1;
+  if (g.K <= 640 + 11 * tiles) return 1;
   int s = (int)std::min<int64_t>(8, 512 / tiles);
   while (s > 1 && (s * mn > g.ws_elems || g.K / s < 512 || !one_round(tiles, s) || (s - 1) * cdiv(slices, s) >= slices))
     --s;

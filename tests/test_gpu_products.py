@@ -46,9 +46,10 @@ def _sum_tol(K):
     (2048, 5632, 2048),   # 176 tiles of 256 x 256: one round of them
     (4096, 14336, 2048),  # 896 tiles of 256 x 256, 3.5 rounds: not deep enough to split the last 128
     (2560, 6912, 2048),   # 270 tiles of 256 x 256: the last 14 split over K
+    (3200, 8704, 2048),   # whole 128 x 128 tiles, 256 x 256 ones partial at the edge
     (768, 3072, 2056),    # the widths of the first over a ragged K: 3 splits, one round
     (128, 10752, 4104),   # 84 tiles over a ragged K: 5 splits (6 would be 80 blocks each)
-], ids=["wide", "one-round", "half-round", "tail", "ragged", "ragged-84"])
+], ids=["wide", "one-round", "half-round", "tail", "edge", "ragged", "ragged-84"])
 def test_weight_gradient_tiles(d, ffn, T):
     import torch
     st, x, dy = _stage(d, ffn, T)
