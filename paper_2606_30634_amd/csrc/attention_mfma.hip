@@ -1139,11 +1139,18 @@ void bwd_launch(const AttnArgs& args, hipStream_t st) {
 }  // namespace
 
 // A dK/dV item walks group x S / 64 tiles of queries, so a few key/value heads leave the chip to the
-// longest items: below 512 items (two per CU) each is split, keeping at least 8 tiles to the longest.
+// longest items: fewer items than the chip holds are split, keeping at least 8 tiles to the longest.  Head
+// dim 64: up to 512 of them (two per CU; the dQ items fill the rest).  Head dim 128, one item per CU: up to
+// 256, and up to 512 where shares of half the length even out more than their partial sums and the second
+// round cost: from 48 tiles on when 256 is a multiple of the items, from 140 on otherwise.  Backward split
+// towards 256 against 512: 256 items of 16 tiles 72 : 89 us, 32 122 : 126, 64 222 : 203, 512 1278 : 957; 384 of
+// 24 103 : 141, 96 314 : 336, 188 577 : 570; 192 of 64 142 : 155, 188 320 : 314; 128 of 32 106 : 111, 64 180 :
+// 173; 64 of 64 82 : 87, 128 134 : 127.
 int attention_dkv_splits(int B, int S, int Hq, int Hkv, int hd) {
   if (hd != 64 && hd != 128) return 1;
   const int64_t items = cdiv(S, QB) * Hkv * B, tiles = (int64_t)(Hq / Hkv) * cdiv(S, KB);
-  return (int)std::max<int64_t>(1, std::min<int64_t>({8, cdiv(512, items), tiles / 8}));
+  const int64_t most = hd == 64 || tiles >= 140 || (tiles >= 48 && 256 % items == 0) ? 512 : 256;
+  return (int)std::max<int64_t>(1, std::min<int64_t>({8, cdiv(most, items), tiles / 8}));
 }
 
 bool attention_mfma_fwd_try(const AttnArgs& a, hipStream_t st) {
